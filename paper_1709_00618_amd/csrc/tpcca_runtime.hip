@@ -500,8 +500,9 @@ static int load_unit(tpcca_ctx *c, int32_t slot, int32_t sector, const tpcca_clu
     if (rc != TPCCA_OK) return rc;
     rc = ensure(c, c->in_row, (size_t)(c->in_used + n), (size_t)c->in_used);
     if (rc != TPCCA_OK) return rc;
-    if (old_cl && old_cl != ptr<float4>(c->in_cl)) {
-      // staged units recorded addresses in the old buffers: rebase them
+    if ((old_cl && old_cl != ptr<float4>(c->in_cl)) || (old_row && old_row != ptr<uint8_t>(c->in_row))) {
+      // staged units recorded addresses in the old buffers: rebase them (the
+      // two buffers grow at different sizes, so either may have moved alone)
       for (auto &V : c->units) {
         if (V.cl >= old_cl && V.cl < old_cl + c->in_used) {
           V.row = ptr<uint8_t>(c->in_row) + (V.row - old_row);
