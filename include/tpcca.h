@@ -222,7 +222,8 @@ int tpcca_batch_totals(tpcca_ctx_t *ctx, int32_t *n_units, int64_t *n_clusters, 
    Kalman row steps (propagations), candidate clusters examined by the
    track-following searches, chi2 tests of the hits those searches picked,
    Kalman updates, the fit kernel's loop iterations summed over its 64-lane
-   waves (fit_steps / (64 x fit_wave_iterations) is its lane use), and, from
+   waves (fit_steps / (64 x fit_wave_iterations) is its lane use; in runs of
+   few tracklets the steps of each wave's longest one, a lower bound), and, from
    the GPU's constant clock, the fit kernel's span and the part of it after
    the first wave found no more tracklets to start (the drain), in ns, summed
    over runs; and the batches since the context was created that ran without
@@ -279,7 +280,7 @@ typedef struct {
   int32_t grid_hits_per_bin; /* z-bin occupancy of the row grid (1); applies after reset */
   int32_t link_blocks_per_cu;/* resident neighbour-finding blocks per CU (0: 32) */
   int32_t fit_min_waves;     /* register budget of the fit kernel in resident waves per SIMD:
-                                0 (5), 4 or 6 (larger values act as 6) */
+                                0 to 4 (4) or 5 (larger values act as 5) */
   int32_t fit_claims;        /* 1: the fit kernel writes the selection's claims as tracklets end
                                 (default); 0: a claim kernel of its own */
   int32_t fit_xcd_slices;    /* 1: the fit's processing order is cut into one slice per XCD;

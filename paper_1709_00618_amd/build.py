@@ -10,7 +10,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(HERE, "libtpcca.so")
-SOURCES = ["tpcca_kernels.hip", "tpcca_fit_rows.hip", "tpcca_runtime.hip", "tpcca_server.hip", "tpcca_phase2.hip"]
+SOURCES = ["tpcca_kernels.hip", "tpcca_fit.hip", "tpcca_fit_rows.hip", "tpcca_runtime.hip", "tpcca_server.hip", "tpcca_phase2.hip"]
 HEADERS = ["tpcca_internal.h", "tpcca_kernels.h", "tpcca_dev.h", "tpcca_kf.h", "tpcca_fit.h", "tpcca_runtime.h", "tpcca_phase2.h"]
 ARCH = os.environ.get("TPCCA_OFFLOAD_ARCH", "gfx950")
 

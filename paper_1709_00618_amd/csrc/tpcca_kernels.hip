@@ -26,8 +26,6 @@
 #include "tpcca_fit.h"
 
 #include <algorithm>
-#include <map>
-#include <mutex>
 
 namespace tpcca {
 
@@ -1055,394 +1053,6 @@ __global__ void k_empty_units(Bufs B, int run) {
   }
 }
 
-// ------------------------------------------------------------ tracklets ---
-// Nearest hit (dy^2 + dz^2, ties to the lower ID) of the row described by t
-// inside the prediction window; -1 if none; its coordinates are returned
-// in bc.
-// The state's z is relative to zr (see k_kf); the bins are looked up around
-// the absolute prediction zr + z with a margin that covers its rounding.
-__device__ __forceinline__ int kf_search(const Bufs &B, const ParamsDev &P, const RowTab &t,
-                                         const KState &s, float zr, unsigned int &cands, float2 &bc) {
-  float wy = P.nsig * sqrtf(s.C[0] + P.ery);
-  float wz = P.nsig * sqrtf(s.C[2] + P.erz);
-  if (wy > P.wmax) wy = P.wmax;
-  if (wz > P.wmax) wz = P.wmax;
-  int b, e;
-  bin_range(t, B.binbeg, zr + s.p[1], wz, b, e);
-  int best = -1;
-  float bd2 = __builtin_inff();
-  cands += (unsigned int)(e - b);
-  // candidates in ascending sorted index, loaded two at a time (independent
-  // loads in flight); the evaluation order is unchanged
-  for (int i0 = b; i0 < e; i0 += 2) {
-    float2 c[2];
-#pragma unroll
-    for (int q = 0; q < 2; ++q) c[q] = i0 + q < e ? B.yz[i0 + q] : make_float2(0.0f, 0.0f);
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      const int i = i0 + q;
-      if (!(i < e && fabsf(c[q].x - s.p[0]) <= wy && fabsf((c[q].y - zr) - s.p[1]) <= wz)) continue;
-      const float dy = c[q].x - s.p[0];
-      const float dz = (c[q].y - zr) - s.p[1];
-      const float d2 = __builtin_fmaf(dy, dy, dz * dz);
-      // equal distances (rare) are decided by the lower cluster ID
-      if (d2 < bd2 || (d2 == bd2 && B.sid[i] < B.sid[best])) {
-        bd2 = d2;
-        best = i;
-        bc = c[q];
-      }
-    }
-  }
-  return best;
-}
-
-// Track following with the Kalman filter (Fig. 1c), one tracklet per lane:
-// seed on the chain's first hit with the direction of its end points; pass 1
-// updates with the chain and follows outward picking the nearest window hit
-// with chi2 <= pick_chi2 (stop after max_miss empty rows); pass 2 restarts at
-// the outermost hit with the pass-1 covariance x refit_inflate, refits inward
-// through all pass-1 hits and continues below the chain start.
-//
-// The state's z is kept relative to zr, the z of the chain's first hit:
-// measurements enter as z_hit - zr (exact for a track's own hits) and the
-// outputs add zr back.  Time frames place z' tens of metres from the
-// sector's origin (Sec. 5), where an absolute FP32 z would carry rounding
-// errors comparable with the fit's resolution.
-//
-// The kernel is persistent and written as a per-lane state machine: every
-// loop iteration performs one row step (propagate, search or take the given
-// hit, update) of whatever phase the lane is in, and a lane whose tracklet
-// is done takes the next one from a device work counter (one atomic per
-// wave).  Lanes of a wave therefore stay busy while tracklets of very
-// different lengths and phases share it; each tracklet still sees exactly
-// the operation sequence of the sequential description above.
-template <int kMinWaves, int kBlk>
-__global__ __launch_bounds__(kBlk, kMinWaves) void k_kf(Bufs B, ParamsDev P, int run) {
-  RunDev &rd = B.runs[run];
-  const int R = P.n_rows;
-  const int n_trk = rd.n_trk;
-  const int lane = threadIdx.x & 63;
-  int phase = kIdle;
-  bool exhausted = false;
-  const int kPool = P.kf_pool;
-  int t = 0, start_id = 0, n_chain = 0, r0 = 0, k = 0, r = 0, miss = 0, n1 = 0, ne = 0;
-  int prev = 0;
-  int u = 0, ucl = 0;  // the tracklet's unit and its first global cluster index
-  float zr = 0.0f;     // z of the chain's first hit: the origin of the state's z
-  // the row positions, staged once per block
-  __shared__ float s_rx[kMaxRows + 1];
-  for (int i = threadIdx.x; i < R; i += blockDim.x) s_rx[i] = B.row_x[i];
-  __syncthreads();
-  KState st;
-  // aux state in LDS (frees registers for occupancy): the pass-1 state at
-  // the outermost hit, then the pass-2 state at the innermost hit
-  __shared__ float s_aux[21][kBlk];
-  const int tid = threadIdx.x;
-  // hit slots go to memory eight at a time (one aligned 32-B group): a lane
-  // collects a group in LDS and writes it when complete or when its phase
-  // ends; the refit reads them back a group at a time.  Scattered stores
-  // narrower than a memory segment cost a read-modify-write each, so fewer,
-  // wider ones matter.
-  constexpr int G = kSlotGrp, GM = kSlotGrp - 1;
-  __shared__ int32_t s_slot[G][kBlk];
-  const int Rs = slot_stride(R);
-  auto slot_flush = [&](int j) {  // the group holding slot j
-    int4 *dst = reinterpret_cast<int4 *>(B.trk_hits + (int64_t)t * Rs + (j & ~GM));
-    dst[0] = make_int4(s_slot[0][tid], s_slot[1][tid], s_slot[2][tid], s_slot[3][tid]);
-    dst[1] = make_int4(s_slot[4][tid], s_slot[5][tid], s_slot[6][tid], s_slot[7][tid]);
-  };
-  auto slot_put = [&](int j, int32_t v) {
-    s_slot[j & GM][tid] = v;
-    if ((j & GM) == GM) slot_flush(j);
-  };
-  auto save_aux = [&]() {
-#pragma unroll
-    for (int q = 0; q < 5; ++q) s_aux[q][tid] = st.p[q];
-#pragma unroll
-    for (int q = 0; q < 15; ++q) s_aux[5 + q][tid] = st.C[q];
-    s_aux[20][tid] = st.x;
-  };
-  float chi2 = 0.0f;
-  unsigned int cands = 0;
-  unsigned int steps = 0, tests = 0, updates = 0, iters = 0;  // wave totals (scalar)
-  const unsigned long long t_start = __builtin_amdgcn_s_memrealtime();
-  int pnext = 0, pend = 0;  // wave-private pool of claimed tracklets
-  // The processing order is cut into one slice per XCD.  Block b runs on
-  // XCD b mod 8, whose waves drain that slice first (its L2 then holds the
-  // hits of a few sectors rather than of all of them) and then help drain
-  // the following slices.
-  const int nsl = P.kf_xcd ? kXcds : 1;
-  int part = blockIdx.x % nsl, tried = 0;
-  int seen = 0;  // the work counter as of this wave's last claim
-  for (;;) {
-    const unsigned long long idle = __ballot(phase == kIdle);
-    while (idle && pnext == pend && !exhausted) {
-      // claim the next tracklets of the slice with one atomic per wave:
-      // kPool neighbouring ones while many remain; in the last stretch
-      // (less than a quarter pool per wave left, judged from this wave's
-      // previous claim) fewer, but never fewer than the idle lanes, so that
-      // at the end no wave holds a private backlog
-      const int lo = (int)((int64_t)n_trk * part / nsl);
-      const int hi = (int)((int64_t)n_trk * (part + 1) / nsl);
-      const int nw = (int)((gridDim.x * blockDim.x) >> 6);
-      const int want = max(__popcll(idle), min(kPool, 4 * (((hi - lo) - seen) / nw)));
-      int base = 0;
-      if (lane == 0) base = atomicAdd(&rd.kf_next[part], want);
-      base = __shfl(base, 0, 64);
-      seen = base + want;
-      if (base < hi - lo) {
-        pnext = lo + base;
-        pend = min(pnext + want, hi);
-      } else if (++tried == nsl) {
-        exhausted = true;
-        if (lane == 0) atomicMin(&rd.kf_t_drain, (unsigned long long)__builtin_amdgcn_s_memrealtime());
-      } else {
-        part = (part + 1) % nsl;
-        seen = 0;
-      }
-    }
-    if (idle && pnext < pend) {
-      const int take = min(__popcll(idle), pend - pnext);
-      const int rank = __popcll(idle & ((1ull << lane) - 1));
-      const int mine = pnext + rank;
-      pnext += take;
-      {
-        if (phase == kIdle) {
-          const int tl = mine;
-          if (rank < take) {
-            t = B.kf_order[rd.trk0 + tl];
-            const int g0 = B.trk_start[t];
-            u = B.trk_unit[t];
-            ucl = B.units[u].cl_begin;
-            const int2 ci = B.cinfo[g0];
-            const int gL = ci.x;
-            n_chain = ci.y;
-            r0 = B.srow[g0];
-            start_id = B.sid[g0];
-            const float2 h0 = B.yz[g0], hL = B.yz[gL];
-            const float x0 = s_rx[r0], xL = s_rx[r0 + n_chain - 1];
-            const float dxs = xL - x0;
-            const float ty = (hL.x - h0.x) / dxs;
-            const float sn = ty / sqrtf(__builtin_fmaf(ty, ty, 1.0f));
-            const float tz = (hL.y - h0.y) / dxs;
-            const float tl2 = tz * sqrtf(__builtin_fmaf(-sn, sn, 1.0f));
-            zr = h0.y;
-            st.p[0] = h0.x;
-            st.p[1] = h0.y - zr;
-            st.p[2] = sn;
-            st.p[3] = tl2;
-            st.p[4] = 0.0f;
-#pragma unroll
-            for (int q = 0; q < 15; ++q) st.C[q] = 0.0f;
-            st.C[0] = P.ery;
-            st.C[2] = P.erz;
-            st.C[5] = P.c22;
-            st.C[9] = P.c33;
-            st.C[14] = P.c44;
-            st.x = x0;
-            s_slot[0][tid] = slot_enc(g0, ucl, r0);
-            prev = g0;
-            k = 1;
-            chi2 = 0.0f;
-            phase = kChain;
-          }
-        }
-      }
-    }
-    if (!__any(phase != kIdle) && exhausted && pnext == pend) break;
-    // ---- inputs of this row step: a given hit to update with, or a search
-    bool act = phase != kIdle;
-    bool prop = act;
-    bool end = false;  // FOLLOW / EXTEND ran out of rows
-    int given = -1;
-    int row = 0;
-    if (phase == kChain) {
-      given = B.upc[prev];
-      row = r0 + k;
-    } else if (phase == kRefit) {
-      if (k == n1 - 1 || (k & GM) == GM) {
-        const int4 *src = reinterpret_cast<const int4 *>(B.trk_hits + (int64_t)t * Rs + (k & ~GM));
-        const int4 q0 = src[0], q1 = src[1];
-        s_slot[0][tid] = q0.x;
-        s_slot[1][tid] = q0.y;
-        s_slot[2][tid] = q0.z;
-        s_slot[3][tid] = q0.w;
-        s_slot[4][tid] = q1.x;
-        s_slot[5][tid] = q1.y;
-        s_slot[6][tid] = q1.z;
-        s_slot[7][tid] = q1.w;
-      }
-      const int32_t v = s_slot[k & GM][tid];
-      given = slot_hit(v, ucl);
-      row = slot_row(v);
-      prop = k < n1 - 1;
-    } else if (phase == kFollow || phase == kExtend) {
-      end = phase == kFollow ? r >= R : r < 0;
-      row = r;
-      if (end) act = prop = false;
-    }
-    // loads that do not depend on the propagation are issued before it, so
-    // that their latency overlaps its arithmetic: the given hit, or the
-    // grid description of the row to search
-    float2 c = make_float2(0.0f, 0.0f);
-    RowTab trow;
-    if (given >= 0) c = B.yz[given];
-    else if (act) trow = B.rowtab[(int64_t)u * (R + 1) + row];
-    // ---- the step: one propagation, one search, one test, one update
-    bool ok = true;
-    steps += __popcll(__ballot(prop));
-    ++iters;
-    if (prop) ok = kf_propagate(P, st, s_rx[row]);
-    int h = given;
-    const bool search = act && ok && given < 0;
-    if (search) h = kf_search(B, P, trow, st, zr, cands, c);
-    const float zm = c.y - zr;
-    bool acc = act && ok && h >= 0;
-    tests += __popcll(__ballot(acc && search));
-    if (acc && search) {
-      float cc2;
-      acc = kf_chi2(P, st, c.x, zm, cc2) && cc2 <= P.pick_chi2;
-    }
-    float c2 = 0.0f;
-    updates += __popcll(__ballot(acc));
-    const bool upd = acc && kf_update(P, st, c.x, zm, c2);
-    bool fin = false;  // a tracklet fit ended with enough hits: claim them
-    // ---- bookkeeping
-    if (phase == kChain) {
-      if (!upd) {
-        kf_fail(B, t, start_id, n_chain);
-        phase = kIdle;
-      } else {
-        slot_put(k, slot_enc(h, ucl, row));
-        prev = h;
-        if (++k == n_chain) {
-          save_aux();
-          r = r0 + n_chain;
-          miss = 0;
-          n1 = n_chain;
-          phase = kFollow;
-        }
-      }
-    } else if (phase == kRefit) {
-      if (!upd) {
-        kf_fail(B, t, start_id, n_chain);
-        phase = kIdle;
-      } else {
-        chi2 = chi2 + c2;
-        if (--k < 0) {
-          save_aux();
-          ne = 0;
-          miss = 0;
-          r = r0 - 1;
-          phase = kExtend;
-        }
-      }
-    } else if (phase == kFollow || phase == kExtend) {
-      const bool fwd = phase == kFollow;
-      if (!end) {
-        if (!ok) {
-          end = true;
-        } else {
-          if (upd) {
-            if (fwd) {
-              slot_put(n1, slot_enc(h, ucl, r));
-              ++n1;
-            } else {
-              chi2 = chi2 + c2;
-              const int j = n1 + ne;
-              if ((j & ~GM) < n1)  // a group shared with pass-1 slots: this slot alone
-                B.trk_hits[(int64_t)t * Rs + j] = slot_enc(h, ucl, r);
-              else
-                slot_put(j, slot_enc(h, ucl, r));
-              ++ne;
-            }
-            save_aux();
-            miss = 0;
-          } else if (++miss >= P.max_miss) {
-            end = true;
-          }
-          r += fwd ? 1 : -1;
-        }
-      }
-      if (end && fwd) {
-        // end of pass 1: its last (partial) slot group goes to memory (the
-        // slots after n1 are written again by pass 2 or never read); keep
-        // the pass-1 state in the record, restart for pass 2
-        if (n1 & GM) slot_flush(n1 - 1);
-        tpcca_tracklet_t &o = B.trk[t];
-#pragma unroll
-        for (int q = 0; q < 5; ++q) o.p_out[q] = st.p[q] = s_aux[q][tid];
-        o.p_out[1] = st.p[1] + zr;
-#pragma unroll
-        for (int q = 0; q < 15; ++q) o.cov_out[q] = st.C[q] = s_aux[5 + q][tid];
-        o.x_out = st.x = s_aux[20][tid];
-        kf_restart(P, st);
-        chi2 = 0.0f;
-        k = n1 - 1;
-        phase = kRefit;
-      } else if (end) {
-        tpcca_tracklet_t &o = B.trk[t];
-        o.start_id = start_id;
-        o.n_chain = n_chain;
-        o.n_hits = n1 + ne;
-        o.n_pass1 = n1;
-        o.ndf = 2 * (n1 + ne) - 5;
-        // the last partial group of pass-2 slots (one that does not share
-        // pass-1 slots) goes to memory
-        const int jl = n1 + ne - 1;
-        if (ne > 0 && (jl & GM) != GM && (jl & ~GM) >= n1) slot_flush(jl);
-        // outermost pass-1 hit and innermost hit, from their slots' rows
-        const int32_t *hl = B.trk_hits + (int64_t)t * Rs;
-        o.row_out = slot_row(hl[n1 - 1]);
-        o.row_ref = ne > 0 ? slot_row(hl[n1 + ne - 1]) : r0;
-        o.x_ref = s_aux[20][tid];
-        o.chi2 = chi2;
-#pragma unroll
-        for (int q = 0; q < 5; ++q) o.p[q] = s_aux[q][tid];
-        o.p[1] = s_aux[1][tid] + zr;
-#pragma unroll
-        for (int q = 0; q < 15; ++q) o.cov[q] = s_aux[5 + q][tid];
-        o.status = (n1 + ne) < P.min_hits ? 1 : 0;
-        fin = o.status == 0;
-        phase = kIdle;
-      }
-    }
-    // ---- the selection's claims of the tracklets that ended in this step:
-    // the wave writes the claim key of each into the owner word of its hits
-    // (one tracklet at a time, hit slots read by all lanes)
-    unsigned long long fm = P.kf_claims ? __ballot(fin) : 0ull;
-    if (fm) {
-      // the hit slots were written by other lanes of this wave
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-      while (fm) {
-        const int src = __builtin_ctzll(fm);
-        fm &= fm - 1;
-        // wave-uniform values of the source lane (scalar registers)
-        const int tt = __builtin_amdgcn_readlane(t, src);
-        const int nn = __builtin_amdgcn_readlane(n1 + ne, src);
-        const unsigned long long kk = claim_key(
-            nn, __int_as_float(__builtin_amdgcn_readlane(__float_as_int(chi2), src)),
-            __builtin_amdgcn_readlane(start_id, src));
-        const int uc = __builtin_amdgcn_readlane(ucl, src);
-        const int32_t *hh = B.trk_hits + (int64_t)tt * Rs;
-        for (int j = lane; j < nn; j += 64) atomicMax(&B.owner[slot_hit(hh[j], uc)], kk);
-      }
-    }
-  }
-  // work counters (one atomic per wave)
-  unsigned long long c64 = wave_sum((unsigned long long)cands);
-  if (lane == 0) {
-    atomicAdd(&rd.kf_steps, (unsigned long long)steps);
-    atomicAdd(&rd.kf_cands, c64);
-    atomicAdd(&rd.kf_tests, (unsigned long long)tests);
-    atomicAdd(&rd.kf_updates, (unsigned long long)updates);
-    atomicAdd(&rd.kf_iters, (unsigned long long)iters);
-    atomicMin(&rd.kf_t_start, t_start);
-    atomicMax(&rd.kf_t_end, (unsigned long long)__builtin_amdgcn_s_memrealtime());
-  }
-}
-
 // ------------------------------------------------------------ selection ---
 __device__ __forceinline__ unsigned long long select_key(const tpcca_tracklet_t &o) {
   return claim_key(o.n_hits, o.chi2, o.start_id);
@@ -1820,76 +1430,6 @@ hipError_t launch_chains(const Bufs &B, const ParamsDev &P, int run, const RunHo
   }
   if (nu > 0) k_empty_units<<<grid_for(nu, 64, 1024), 64, 0, s>>>(B, run);
   if (P.kf_rows > 0) return launch_kf_order_rows(B, P, run, h, s);
-  return hipGetLastError();
-}
-
-// Compute units and resident fit blocks per CU of the current device, for
-// each register variant and block size; queried once per device (contexts
-// on several host threads launch concurrently, hence the lock).
-struct KfOccupancy {
-  int cus = 1;
-  int per[3][3] = {{1, 1, 1}, {1, 1, 1}, {1, 1, 1}};  // [register variant][64, 128, 256 threads]
-};
-
-template <int kBlk>
-static void kf_occ_row(int per[3]) {
-  (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&per[0], k_kf<5, kBlk>, kBlk, 0);
-  (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&per[1], k_kf<4, kBlk>, kBlk, 0);
-  (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&per[2], k_kf<6, kBlk>, kBlk, 0);
-}
-
-static const KfOccupancy &kf_occupancy() {
-  static std::mutex mu;
-  static std::map<int, KfOccupancy> cache;
-  int dev = 0;
-  (void)hipGetDevice(&dev);
-  std::lock_guard<std::mutex> lock(mu);
-  auto it = cache.find(dev);
-  if (it != cache.end()) return it->second;
-  KfOccupancy o;
-  int cus = 0, per[3][3] = {};
-  (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-  kf_occ_row<64>(per[0]);
-  kf_occ_row<128>(per[1]);
-  kf_occ_row<256>(per[2]);
-  o.cus = std::max(1, cus);
-  for (int v = 0; v < 3; ++v)
-    for (int b = 0; b < 3; ++b) o.per[v][b] = std::max(1, per[b][v]);
-  return cache.emplace(dev, o).first->second;
-}
-
-hipError_t launch_kf(const Bufs &B, const ParamsDev &P, int run, const RunHost &h, hipStream_t s) {
-  // persistent: exactly the resident capacity of the chip, work taken from a
-  // counter
-  // register budgets: 5 (default), 4 or 6 resident waves per SIMD; block
-  // sizes 64, 128 (default) or 256 threads
-  const int v = P.kf_min_waves >= 6 ? 2 : P.kf_min_waves == 4 ? 1 : 0;
-  const int blk = kf_block_of(P);
-  const int bi = blk == 64 ? 0 : blk == 256 ? 2 : 1;
-  const KfOccupancy &o = kf_occupancy();
-  const int cus = o.cus;
-  const int bpc = P.kf_blocks_per_cu > 0 ? std::min(P.kf_blocks_per_cu, o.per[v][bi]) : o.per[v][bi];
-  const int g = grid_for(h.trk_cap, blk, cus * bpc);
-  // the claim words of the selection start at zero (the fit may write them
-  // as its tracklets end)
-  hipError_t e = launch_fill_u64(B.owner + h.cl0, h.cl1 - h.cl0, 0ull, s);
-  if (e != hipSuccess) return e;
-  if (P.kf_rows > 0) return launch_kf_rows(B, P, run, h, s);
-  if (h.trk_cap > 0) {
-#define TPCCA_KF(W, T) k_kf<W, T><<<g, T, 0, s>>>(B, P, run)
-    switch (v * 3 + bi) {
-      case 0: TPCCA_KF(5, 64); break;
-      case 2: TPCCA_KF(5, 256); break;
-      case 3: TPCCA_KF(4, 64); break;
-      case 4: TPCCA_KF(4, 128); break;
-      case 5: TPCCA_KF(4, 256); break;
-      case 6: TPCCA_KF(6, 64); break;
-      case 7: TPCCA_KF(6, 128); break;
-      case 8: TPCCA_KF(6, 256); break;
-      default: TPCCA_KF(5, 128); break;
-    }
-#undef TPCCA_KF
-  }
   return hipGetLastError();
 }
 

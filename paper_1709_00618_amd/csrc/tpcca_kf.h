@@ -25,12 +25,14 @@ struct KState {
 // arc length (signed like dx) is the chord times the Maclaurin series of
 // asin(u)/u to u^8, u = chord |k| / 2.  The Jacobian is the simplified one
 // that drops the curvature term of the arc length.  C <- F C F^T.
-__device__ __forceinline__ bool kf_propagate(const ParamsDev &P, KState &s, float x1) {
+// The step itself, for a caller that has no use for the state once the track
+// turned back (|sin phi| beyond the limit, where the state ends up undefined):
+// without a way round it, the new state takes the old one's registers.
+__device__ __forceinline__ bool kf_step(const ParamsDev &P, KState &s, float x1) {
   const float dx = x1 - s.x;
   const float kk = P.kB * s.p[4];
   const float s0 = s.p[2];
   const float s1 = __builtin_fmaf(kk, dx, s0);
-  if (!(fabsf(s1) <= P.max_sin)) return false;
   const float c0 = sqrtf(__builtin_fmaf(-s0, s0, 1.0f));
   const float c1 = sqrtf(__builtin_fmaf(-s1, s1, 1.0f));
   const float cc = c0 + c1;
@@ -93,53 +95,52 @@ __device__ __forceinline__ bool kf_propagate(const ParamsDev &P, KState &s, floa
   C[12] = c42 + f * c44;
   C[13] = c43;
   C[14] = c44;
-  return true;
+  return fabsf(s1) <= P.max_sin;
 }
 
-// chi2 of a 2-D measurement against the state (S = C_yz + R).
-__device__ __forceinline__ bool kf_chi2(const ParamsDev &P, const KState &s, float ym, float zm,
-                                        float &chi2) {
-  const float r0 = ym - s.p[0];
-  const float r1 = zm - s.p[1];
+// As kf_step, the state left as it is when the step fails.
+__device__ __forceinline__ bool kf_propagate(const ParamsDev &P, KState &s, float x1) {
+  const float s1 = __builtin_fmaf(P.kB * s.p[4], x1 - s.x, s.p[2]);
+  if (!(fabsf(s1) <= P.max_sin)) return false;
+  return kf_step(P, s, x1);
+}
+
+// A 2-D measurement against the state: residual, inverse of S = C_yz + R and
+// chi2.  The test of a searched hit and the update with it share it.  Fails
+// (its values undefined) unless det S > 0.
+struct KMeas {
+  float r0, r1, i00, i10, i11, chi2;
+};
+__device__ __forceinline__ bool kf_meas(const ParamsDev &P, const KState &s, float ym, float zm, KMeas &m) {
+  m.r0 = ym - s.p[0];
+  m.r1 = zm - s.p[1];
   const float s00 = s.C[0] + P.ery;
   const float s10 = s.C[1];
   const float s11 = s.C[2] + P.erz;
   const float det = s00 * s11 - s10 * s10;
-  if (!(det > 0.0f)) return false;
   const float inv = 1.0f / det;
-  const float i00 = s11 * inv, i10 = -s10 * inv, i11 = s00 * inv;
-  const float v0 = i00 * r0 + i10 * r1;
-  const float v1 = i10 * r0 + i11 * r1;
-  chi2 = r0 * v0 + r1 * v1;
-  return true;
+  m.i00 = s11 * inv;
+  m.i10 = -s10 * inv;
+  m.i11 = s00 * inv;
+  const float v0 = m.i00 * m.r0 + m.i10 * m.r1;
+  const float v1 = m.i10 * m.r0 + m.i11 * m.r1;
+  m.chi2 = m.r0 * v0 + m.r1 * v1;
+  return det > 0.0f;
 }
 
-// Kalman update with (ym, zm): K = C H^T S^-1, p += K r, C -= K H C.
-__device__ __forceinline__ bool kf_update(const ParamsDev &P, KState &s, float ym, float zm,
-                                          float &chi2) {
-  const float r0 = ym - s.p[0];
-  const float r1 = zm - s.p[1];
-  const float s00 = s.C[0] + P.ery;
-  const float s10 = s.C[1];
-  const float s11 = s.C[2] + P.erz;
-  const float det = s00 * s11 - s10 * s10;
-  if (!(det > 0.0f)) return false;
-  const float inv = 1.0f / det;
-  const float i00 = s11 * inv, i10 = -s10 * inv, i11 = s00 * inv;
-  const float v0 = i00 * r0 + i10 * r1;
-  const float v1 = i10 * r0 + i11 * r1;
-  chi2 = r0 * v0 + r1 * v1;
+// Kalman gain with a measurement: K = C H^T S^-1, p += K r, C -= K H C.
+__device__ __forceinline__ void kf_gain(KState &s, const KMeas &m) {
   // first two columns of C (old values), row k = (C_k0, C_k1)
   const float cj0[5] = {s.C[0], s.C[1], s.C[3], s.C[6], s.C[10]};
   const float cj1[5] = {s.C[1], s.C[2], s.C[4], s.C[7], s.C[11]};
   float k0[5], k1[5];
 #pragma unroll
   for (int k = 0; k < 5; ++k) {
-    k0[k] = cj0[k] * i00 + cj1[k] * i10;
-    k1[k] = cj0[k] * i10 + cj1[k] * i11;
+    k0[k] = cj0[k] * m.i00 + cj1[k] * m.i10;
+    k1[k] = cj0[k] * m.i10 + cj1[k] * m.i11;
   }
 #pragma unroll
-  for (int k = 0; k < 5; ++k) s.p[k] = s.p[k] + k0[k] * r0 + k1[k] * r1;
+  for (int k = 0; k < 5; ++k) s.p[k] = s.p[k] + k0[k] * m.r0 + k1[k] * m.r1;
   int idx = 0;
 #pragma unroll
   for (int i = 0; i < 5; ++i)
@@ -148,6 +149,20 @@ __device__ __forceinline__ bool kf_update(const ParamsDev &P, KState &s, float y
       s.C[idx] = s.C[idx] - (k0[i] * cj0[j] + k1[i] * cj1[j]);
       ++idx;
     }
+}
+
+__device__ __forceinline__ bool kf_chi2(const ParamsDev &P, const KState &s, float ym, float zm, float &chi2) {
+  KMeas m;
+  if (!kf_meas(P, s, ym, zm, m)) return false;
+  chi2 = m.chi2;
+  return true;
+}
+
+__device__ __forceinline__ bool kf_update(const ParamsDev &P, KState &s, float ym, float zm, float &chi2) {
+  KMeas m;
+  if (!kf_meas(P, s, ym, zm, m)) return false;
+  chi2 = m.chi2;
+  kf_gain(s, m);
   return true;
 }
 

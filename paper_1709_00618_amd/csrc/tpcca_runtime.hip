@@ -154,6 +154,9 @@ static int copy_sync(tpcca_ctx *c, void *dst, const void *src, size_t bytes, hip
   return TPCCA_OK;
 }
 
+// Some kernels read a buffer's last element with a wider load.
+constexpr size_t kReadSlack = 16;
+
 // Grow a device buffer to at least `bytes` (x1.25 headroom), preserving the
 // first `keep` bytes.  Budget-checked.
 static int ensure(tpcca_ctx *c, DevBuf &b, size_t bytes, size_t keep) {
@@ -171,7 +174,7 @@ static int ensure(tpcca_ctx *c, DevBuf &b, size_t bytes, size_t keep) {
   // context's graph capture
   std::lock_guard<std::recursive_mutex> lock(tpcca::device_ops_lock());
   void *p = nullptr;
-  hipError_t e = hipMalloc(&p, nb);
+  hipError_t e = hipMalloc(&p, nb + kReadSlack);
   if (e != hipSuccess) {
     (void)hipGetLastError();
     c->last_error = std::string("hipMalloc: ") + hipGetErrorString(e);
