@@ -130,8 +130,11 @@ __device__ __forceinline__ void pool_claim(const ParamsDev &P, Pool &p, int32_t 
 // prediction zr + z with a margin that covers its rounding.
 __device__ __forceinline__ int kf_search(const Bufs &B, const ParamsDev &P, const RowTab &t,
                                          const KState &s, float zr, unsigned int &cands, float2 &bc) {
-  float wy = P.nsig * sqrtf(s.C[0] + P.ery);
-  float wz = P.nsig * sqrtf(s.C[2] + P.erz);
+  // with cluster variances the roots' arguments are in kf_sqrt's range
+  const bool mid = P.ery >= 0x1p-96f && P.erz >= 0x1p-96f;
+  const float vy = s.C[0] + P.ery, vz = s.C[2] + P.erz;
+  float wy = P.nsig * (mid ? kf_sqrt(vy) : sqrtf(vy));
+  float wz = P.nsig * (mid ? kf_sqrt(vz) : sqrtf(vz));
   if (wy > P.wmax) wy = P.wmax;
   if (wz > P.wmax) wz = P.wmax;
   int b, e;

@@ -12,6 +12,39 @@
 
 namespace tpcca {
 
+// Correctly rounded division and square root in fewer instructions than the
+// general ones (quotient 4 after 3 for the reciprocal, which quotients by the
+// same number share, against 11; root 7 against 16), for operands in the
+// middle of the exponent range.  A step holds seven quotients by four numbers
+// and three roots, and its instructions are what bounds the fit of few
+// tracklets and keeps its VALU half busy on many.
+//   reciprocal  v_rcp_f32 (1 ulp) and one Newton step; equal to the correctly
+//               rounded one for every 24-bit significand (all checked)
+//   quotient    Markstein's: with the correctly rounded reciprocal r, q = n r
+//               corrected once by its exact residual is correctly rounded
+//               (IBM J. Res. Dev. 34, 1990); v_div_fixup_f32 gives zeros,
+//               infinities and NaN their results.  Exact while n and the
+//               quotient lie above 2^-102 (below, the residual underflows).
+//   root        v_sqrt_f32 (1 ulp) corrected once by its exact residual over
+//               twice the root; equal to the correctly rounded one for every
+//               float from 2^-96 to 2^120 (all checked), 0 and infinity.
+struct KRecip {
+  float d, r;
+};
+__device__ __forceinline__ KRecip kf_recip(float d) {
+  const float r = __builtin_amdgcn_rcpf(d);
+  return {d, __builtin_fmaf(__builtin_fmaf(-d, r, 1.0f), r, r)};
+}
+__device__ __forceinline__ float kf_div(float n, const KRecip &k) {
+  const float q = n * k.r;
+  return __builtin_amdgcn_div_fixupf(__builtin_fmaf(__builtin_fmaf(-k.d, q, n), k.r, q), k.d, n);
+}
+__device__ __forceinline__ float kf_sqrt(float x) {
+  const float g = __builtin_amdgcn_sqrtf(x), h = 0.5f * __builtin_amdgcn_rsqf(x);
+  const float q = __builtin_fmaf(__builtin_fmaf(-g, g, x), h, g);
+  return __builtin_amdgcn_classf(x, 0x260) ? x : q;  // +-0, +infinity
+}
+
 // Track state at plane x: p = (y, z, sin phi, tan lambda, q/pT), C lower
 // triangle (00,10,11,20,21,22,30,31,32,33,40,41,42,43,44).
 struct KState {
@@ -33,13 +66,13 @@ __device__ __forceinline__ bool kf_step(const ParamsDev &P, KState &s, float x1)
   const float kk = P.kB * s.p[4];
   const float s0 = s.p[2];
   const float s1 = __builtin_fmaf(kk, dx, s0);
-  const float c0 = sqrtf(__builtin_fmaf(-s0, s0, 1.0f));
-  const float c1 = sqrtf(__builtin_fmaf(-s1, s1, 1.0f));
-  const float cc = c0 + c1;
-  const float tt = (s0 + s1) / cc;
+  const float c0 = kf_sqrt(__builtin_fmaf(-s0, s0, 1.0f));
+  const float c1 = kf_sqrt(__builtin_fmaf(-s1, s1, 1.0f));
+  const KRecip rc0 = kf_recip(c0), rc1 = kf_recip(c1), rcc = kf_recip(c0 + c1);
+  const float tt = kf_div(s0 + s1, rcc);
   const float dy = dx * tt;
   const float ch2 = __builtin_fmaf(dy, dy, dx * dx);
-  const float ch = sqrtf(ch2);
+  const float ch = kf_sqrt(ch2);
   const float chs = dx < 0.0f ? -ch : ch;
   const float u2 = ch2 * kk * kk * 0.25f;
   float h = (float)(35.0 / 1152.0);
@@ -50,9 +83,9 @@ __device__ __forceinline__ bool kf_step(const ParamsDev &P, KState &s, float x1)
   const float dS = chs * h;
   const float t = s.p[3];
 
-  const float a = dx * (2.0f + tt * (s0 / c0 + s1 / c1)) / cc;
-  const float b = dx * P.kB * dx * (1.0f + tt * s1 / c1) / cc;
-  const float g = ch > 0.0f ? t * (dy / chs) : 0.0f;
+  const float a = kf_div(dx * (2.0f + tt * (kf_div(s0, rc0) + kf_div(s1, rc1))), rcc);
+  const float b = kf_div(dx * P.kB * dx * (1.0f + kf_div(tt * s1, rc1)), rcc);
+  const float g = ch > 0.0f ? t * kf_div(dy, kf_recip(chs)) : 0.0f;
   const float cz = g * a;
   const float dzq = g * b;
   const float e = dS;
@@ -118,7 +151,7 @@ __device__ __forceinline__ bool kf_meas(const ParamsDev &P, const KState &s, flo
   const float s10 = s.C[1];
   const float s11 = s.C[2] + P.erz;
   const float det = s00 * s11 - s10 * s10;
-  const float inv = 1.0f / det;
+  const float inv = kf_div(1.0f, kf_recip(det));
   m.i00 = s11 * inv;
   m.i10 = -s10 * inv;
   m.i11 = s00 * inv;
