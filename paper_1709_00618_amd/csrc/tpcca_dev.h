@@ -37,6 +37,25 @@ __device__ __forceinline__ int wave_max_dpp(int v) {
   return __builtin_amdgcn_readlane(v, 63);
 }
 
+// Inclusive sum over the lanes up to this one (all lanes active), the same way.
+__device__ __forceinline__ int wave_scan_dpp(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);  // row_shr:1
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);  // row_shr:2
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);  // row_shr:4
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);  // row_shr:8
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // row_bcast:15
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);  // row_bcast:31
+  return v;
+}
+
+// Orders this wave's LDS accesses before the call against those after it
+// (LDS serves a wave in order; the compiler has to keep the order too).
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Block-wide exclusive scan of one value per thread (blockDim.x <= 1024,
 // multiple of 64).  Returns the exclusive prefix; *total gets the sum.
 template <typename T>

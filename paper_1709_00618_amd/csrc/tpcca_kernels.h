@@ -12,8 +12,23 @@ struct RunHost {
   int64_t bin0, bin1;
   int32_t trk0, trk_cap;
   int32_t tile0, tile1;
-  int32_t dense;  // mean pad-row occupancy of the batch's units >= 1024 (row sort variant)
+  int32_t rows;  // how full the pad rows of the run's units are: a RowClass
 };
+
+// By mean hits in a pad row: which kernels sort the rows and search the
+// neighbours.  The lines lie where the two kernels on their sides meet on time
+// frames of few events (45 hits in a row per event; us):
+//   neighbours, wave per tile / block per tile: 21 / 24 at 90 hits, 64 / 33 at
+//     140 (a wave takes the 64-hit lots of its tile one after the other);
+//   row sort, wave per row / block of 256: 18 / 30 at 270 hits, 55 / 34 at 360
+//     (rows above 512 hits leave the wave form);
+//   row sort, block of 256 / staged in LDS: at 1024 hits a row begins to fill
+//     the staging block.
+enum RowClass { kRowsSparse, kRowsShort, kRowsLong, kRowsDense };
+inline int row_class(int64_t units, int64_t hits, int R) {
+  const int64_t rows = units * (R + 1);
+  return hits < rows * 96 ? kRowsSparse : hits < rows * 300 ? kRowsShort : hits < rows * 1024 ? kRowsLong : kRowsDense;
+}
 
 hipError_t launch_fill_i32(int32_t *p, int64_t n, int32_t v, hipStream_t s);
 hipError_t launch_fill_u64(unsigned long long *p, int64_t n, unsigned long long v, hipStream_t s);

@@ -316,116 +316,194 @@ __global__ __launch_bounds__(kBlock) void k_rowscatter(Bufs B, int run, int R) {
 // different banks.
 __device__ __forceinline__ int hpad(int k) { return k + (k >> 5); }
 
-// Pass 4, one block per (unit, row): counting sort of the row's records by
-// z bin in LDS; writes the row's bin offsets and its sorted hits.
-//   kStage false (sparse rows, kT = 256): the records are read twice (count,
-//     then scatter) and scattered straight into the row's own segment.
+// Pass 4: counting sort of each row's records by z bin; writes the row's bin
+// offsets and its sorted hits.
+//
+// By a block (kT threads):
+//   kStage false: the records are read twice (count, then scatter) and
+//     scattered straight into the row's own segment.
 //   kStage true (dense rows, kT = 1024, one block per CU by its LDS): a row
 //     of up to kT * 8 records is read once into registers, sorted into LDS
 //     and written out in order, so that no partially written line leaves
 //     L2; a longer row takes the scatter path.
 template <int kT, bool kStage>
+struct RowStage {
+  static constexpr int per = 8, cap = kStage ? kT * per : 1;
+  float2 yz[cap];
+  int32_t sid[cap];
+  uint8_t row[cap];
+};
+
+template <int kT, bool kStage>
+__device__ __forceinline__ void row_sort_block(const Bufs &B, const RowTab &t, int *hist, int *lds,
+                                               RowStage<kT, kStage> &S) {
+  constexpr int kPer = RowStage<kT, kStage>::per, kCap = RowStage<kT, kStage>::cap;
+  constexpr int per = kMaxBinsRow / kT;
+  for (int k = threadIdx.x; k < t.nb; k += blockDim.x) hist[hpad(k)] = 0;
+  __syncthreads();
+  const bool staged = kStage && t.count <= kCap;  // uniform over the block
+  int4 rec[kStage ? kPer : 1];
+  int bin[kStage ? kPer : 1];
+  if (staged) {
+#pragma unroll
+    for (int q = 0; q < (kStage ? kPer : 1); ++q) {
+      const int i = threadIdx.x + q * kT;
+      if (i < t.count) rec[q] = B.rtmp[t.begin + i];
+    }
+#pragma unroll
+    for (int q = 0; q < (kStage ? kPer : 1); ++q) {
+      const int i = threadIdx.x + q * kT;
+      if (i < t.count) {
+        bin[q] = zbin(t, __int_as_float(rec[q].y));
+        atomicAdd(&hist[hpad(bin[q])], 1);
+      }
+    }
+  } else {
+#pragma unroll 4
+    for (int i = threadIdx.x; i < t.count; i += blockDim.x) {
+      const int4 r4 = B.rtmp[t.begin + i];
+      atomicAdd(&hist[hpad(zbin(t, __int_as_float(r4.y)))], 1);
+    }
+  }
+  __syncthreads();
+  // exclusive scan of the nb bin counts (per consecutive entries per thread)
+  int v[per];
+  int loc = 0;
+  for (int q = 0; q < per; ++q) {
+    const int k = threadIdx.x * per + q;
+    v[q] = k < t.nb ? hist[hpad(k)] : 0;
+    loc += v[q];
+  }
+  int tot;
+  int ex = block_exclusive_scan<int>(loc, lds, &tot);
+  for (int q = 0; q < per; ++q) {
+    const int k = threadIdx.x * per + q;
+    if (k < t.nb) hist[hpad(k)] = ex;
+    ex += v[q];
+  }
+  __syncthreads();
+  // bin begins, written in coalesced order
+  for (int k = threadIdx.x; k < t.nb; k += blockDim.x) B.binbeg[t.bin0 + k] = t.begin + hist[hpad(k)];
+  if (threadIdx.x == 0) B.binbeg[t.bin0 + t.nb] = t.begin + t.count;
+  __syncthreads();  // every begin is read before the scatter moves the cursors
+  if (staged) {
+#pragma unroll
+    for (int q = 0; q < (kStage ? kPer : 1); ++q) {
+      const int i = threadIdx.x + q * kT;
+      if (i < t.count) {
+        const int pos = atomicAdd(&hist[hpad(bin[q])], 1);
+        S.yz[pos] = make_float2(__int_as_float(rec[q].x), __int_as_float(rec[q].y));
+        S.sid[pos] = rec[q].z;
+        S.row[pos] = (uint8_t)rec[q].w;
+      }
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < t.count; i += blockDim.x) {
+      B.yz[t.begin + i] = S.yz[i];
+      B.sid[t.begin + i] = S.sid[i];
+      B.srow[t.begin + i] = S.row[i];
+    }
+  } else {
+#pragma unroll 4
+    for (int i = threadIdx.x; i < t.count; i += blockDim.x) {
+      const int4 r4 = B.rtmp[t.begin + i];
+      const float z = __int_as_float(r4.y);
+      const int pos = t.begin + atomicAdd(&hist[hpad(zbin(t, z))], 1);
+      B.yz[pos] = make_float2(__int_as_float(r4.x), z);
+      B.sid[pos] = r4.z;
+      B.srow[pos] = (uint8_t)r4.w;
+    }
+  }
+  __syncthreads();
+}
+
+template <int kT, bool kStage>
 __global__ __launch_bounds__(kT) void k_rowsort(Bufs B, int run, int R) {
-  constexpr int kPer = 8, kCap = kStage ? kT * kPer : 1;
   __shared__ int hist[kMaxBinsRow + kMaxBinsRow / 32];
   __shared__ int lds[kT / 64 + 1];
-  __shared__ float2 s_yz[kCap];
-  __shared__ int32_t s_sid[kCap];
-  __shared__ uint8_t s_row[kCap];
+  __shared__ RowStage<kT, kStage> S;
   const RunDev &rd = B.runs[run];
   const int nrows = (rd.u1 - rd.u0) * (R + 1);
-  constexpr int per = kMaxBinsRow / kT;
   for (int w = blockIdx.x; w < nrows; w += gridDim.x) {
-    const int64_t rr = (int64_t)rd.u0 * (R + 1) + w;
-    const RowTab t = B.rowtab[rr];
-    for (int k = threadIdx.x; k < t.nb; k += blockDim.x) hist[hpad(k)] = 0;
-    __syncthreads();
-    const bool staged = kStage && t.count <= kCap;  // uniform over the block
-    int4 rec[kStage ? kPer : 1];
-    int bin[kStage ? kPer : 1];
-    if (staged) {
-#pragma unroll
-      for (int q = 0; q < (kStage ? kPer : 1); ++q) {
-        const int i = threadIdx.x + q * kT;
-        if (i < t.count) rec[q] = B.rtmp[t.begin + i];
-      }
-#pragma unroll
-      for (int q = 0; q < (kStage ? kPer : 1); ++q) {
-        const int i = threadIdx.x + q * kT;
-        if (i < t.count) {
-          bin[q] = zbin(t, __int_as_float(rec[q].y));
-          atomicAdd(&hist[hpad(bin[q])], 1);
-        }
-      }
-    } else {
-#pragma unroll 4
-      for (int i = threadIdx.x; i < t.count; i += blockDim.x) {
-        const int4 r4 = B.rtmp[t.begin + i];
-        atomicAdd(&hist[hpad(zbin(t, __int_as_float(r4.y)))], 1);
-      }
-    }
-    __syncthreads();
-    // exclusive scan of the nb bin counts (per consecutive entries per thread)
-    int v[per];
-    int loc = 0;
-    for (int q = 0; q < per; ++q) {
-      const int k = threadIdx.x * per + q;
-      v[q] = k < t.nb ? hist[hpad(k)] : 0;
-      loc += v[q];
-    }
-    int tot;
-    int ex = block_exclusive_scan<int>(loc, lds, &tot);
-    for (int q = 0; q < per; ++q) {
-      const int k = threadIdx.x * per + q;
-      if (k < t.nb) hist[hpad(k)] = ex;
-      ex += v[q];
-    }
-    __syncthreads();
-    // bin begins, written in coalesced order
-    for (int k = threadIdx.x; k < t.nb; k += blockDim.x) B.binbeg[t.bin0 + k] = t.begin + hist[hpad(k)];
-    if (threadIdx.x == 0) B.binbeg[t.bin0 + t.nb] = t.begin + t.count;
-    __syncthreads();  // every begin is read before the scatter moves the cursors
-    if (staged) {
-#pragma unroll
-      for (int q = 0; q < (kStage ? kPer : 1); ++q) {
-        const int i = threadIdx.x + q * kT;
-        if (i < t.count) {
-          const int pos = atomicAdd(&hist[hpad(bin[q])], 1);
-          s_yz[pos] = make_float2(__int_as_float(rec[q].x), __int_as_float(rec[q].y));
-          s_sid[pos] = rec[q].z;
-          s_row[pos] = (uint8_t)rec[q].w;
-        }
-      }
-      __syncthreads();
-      for (int i = threadIdx.x; i < t.count; i += blockDim.x) {
-        B.yz[t.begin + i] = s_yz[i];
-        B.sid[t.begin + i] = s_sid[i];
-        B.srow[t.begin + i] = s_row[i];
-      }
-    } else {
-#pragma unroll 4
-      for (int i = threadIdx.x; i < t.count; i += blockDim.x) {
-        const int4 r4 = B.rtmp[t.begin + i];
-        const float z = __int_as_float(r4.y);
-        const int pos = t.begin + atomicAdd(&hist[hpad(zbin(t, z))], 1);
-        B.yz[pos] = make_float2(__int_as_float(r4.x), z);
-        B.sid[pos] = r4.z;
-        B.srow[pos] = (uint8_t)r4.w;
-      }
-    }
-    __syncthreads();
+    const RowTab t = B.rowtab[(int64_t)rd.u0 * (R + 1) + w];
+    row_sort_block<kT, kStage>(B, t, hist, lds, S);
   }
 }
 
-// Row of sorted hit g from the unit's row table held in LDS.
-__device__ __forceinline__ int row_of(const RowTab *t, int R, int g) {
-  int lo = 0, hi = R;  // rows 0..R; find last row with begin <= g
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (t[mid].begin <= g) lo = mid;
-    else hi = mid - 1;
+// By a wave: a row of at most kWaveRow records and bins, read once into
+// registers; the LDS counter that a record adds to also gives its rank in its
+// bin, and no barrier is needed.  A block per row of 46 records (64
+// minimum-bias events, 370 thousand rows) keeps one wave in four busy between
+// seven barriers: 1180 us; sixteen rows to a block: 260 us (0.67 GB: 2.6 TB/s).
+constexpr int kWaveRow = 512;
+
+__device__ __forceinline__ void row_sort_wave(const Bufs &B, const RowTab &t, int *hist) {
+  constexpr int kPer = kWaveRow / 64;
+  const int lane = threadIdx.x & 63;
+  for (int k = lane; k < t.nb; k += 64) hist[hpad(k)] = 0;
+  int4 rec[kPer];
+  int bin[kPer], rank[kPer];
+#pragma unroll
+  for (int q = 0; q < kPer; ++q)
+    if (lane + q * 64 < t.count) rec[q] = B.rtmp[t.begin + lane + q * 64];
+  wave_lds_order();
+#pragma unroll
+  for (int q = 0; q < kPer; ++q)
+    if (lane + q * 64 < t.count) {
+      bin[q] = hpad(zbin(t, __int_as_float(rec[q].y)));
+      rank[q] = atomicAdd(&hist[bin[q]], 1);
+    }
+  wave_lds_order();
+  int before = t.begin;  // records of the bins passed
+  for (int k0 = 0; k0 < t.nb; k0 += 64) {
+    const int k = k0 + lane;
+    const int v = k < t.nb ? hist[hpad(k)] : 0;
+    const int incl = wave_scan_dpp(v);
+    if (k < t.nb) {
+      const int beg = before + incl - v;
+      hist[hpad(k)] = beg;
+      B.binbeg[t.bin0 + k] = beg;
+    }
+    before += __builtin_amdgcn_readlane(incl, 63);
   }
-  return lo;
+  if (lane == 0) B.binbeg[t.bin0 + t.nb] = t.begin + t.count;
+  wave_lds_order();
+#pragma unroll
+  for (int q = 0; q < kPer; ++q)
+    if (lane + q * 64 < t.count) {
+      const int pos = hist[bin[q]] + rank[q];
+      B.yz[pos] = make_float2(__int_as_float(rec[q].x), __int_as_float(rec[q].y));
+      B.sid[pos] = rec[q].z;
+      B.srow[pos] = (uint8_t)rec[q].w;
+    }
+  wave_lds_order();  // the next row clears the counters
+}
+
+// Rows that are not dense: sixteen rows at a time, a wave each; the ones too
+// long for a wave are then sorted by the whole block.
+__global__ __launch_bounds__(1024) void k_rowsort_waves(Bufs B, int run, int R) {
+  constexpr int kT = 1024, kWaves = kT / 64, kHist = kWaveRow + kWaveRow / 32;
+  __shared__ int hist[kWaves * kHist];  // the block's histogram takes the same words
+  static_assert(kWaves * kHist >= kMaxBinsRow + kMaxBinsRow / 32, "block histogram");
+  __shared__ int lds[kWaves + 1];
+  __shared__ RowStage<kT, false> S;
+  const RunDev &rd = B.runs[run];
+  const RowTab *rows = B.rowtab + (int64_t)rd.u0 * (R + 1);
+  const int nrows = (rd.u1 - rd.u0) * (R + 1);
+  const int wid = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  for (int w0 = blockIdx.x * kWaves; w0 < nrows; w0 += gridDim.x * kWaves) {
+    bool longer = false;
+    if (w0 + wid < nrows) {
+      const RowTab t = rows[w0 + wid];
+      longer = t.count > kWaveRow || t.nb > kWaveRow;
+      if (!longer) row_sort_wave(B, t, hist + wid * kHist);
+    }
+    if (__syncthreads_or(longer ? 1 : 0))
+      for (int w = w0; w < min(nrows, w0 + kWaves); ++w) {
+        const RowTab t = rows[w];
+        if (t.count > kWaveRow || t.nb > kWaveRow) row_sort_block<kT, false>(B, t, hist, lds, S);
+      }
+  }
 }
 
 // ---------------------------------------------------------------- links ---
@@ -438,8 +516,6 @@ __device__ __forceinline__ int row_of(const RowTab *t, int R, int g) {
 // are a contiguous range of sorted hits; they are staged in LDS with their
 // bin offsets, so every candidate test reads LDS.  Tiles whose neighbour
 // ranges exceed the LDS capacity read the candidates from global memory.
-// Tiles are walked XCD by XCD so that neighbouring rows of a unit share an
-// L2.
 // Staging capacities come in variants (tuning knob link_stage): larger ones
 // fall back to global memory less often, smaller ones let more blocks share
 // a CU's LDS.  Variant 0 takes 19.5 KB of LDS; the kernel is held to 72
@@ -601,6 +677,15 @@ __device__ __forceinline__ LinkBest link_hit_lds(const Bufs &B, float2 h, float 
   return b;
 }
 
+// The walk: blocks b with b % 8 == x (one XCD) take every eighth group of
+// tiles, so that neighbouring rows share an L2 and no XCD gets all the rows of
+// a large event (with an eighth of the tiles in one piece 64 minimum-bias
+// events took 1302 us instead of 610, two XCDs working at the end).
+__device__ __forceinline__ int xcd_tile(int j) {
+  constexpr int kGroupTiles = 128;
+  return (j / kGroupTiles * 8 + (int)(blockIdx.x & 7)) * kGroupTiles + j % kGroupTiles;
+}
+
 template <int kV, int kT>
 __global__ __launch_bounds__(kT, 7) void k_links(Bufs B, ParamsDev P, int run) {
   constexpr int kNbrCap = LinkCaps<kV>::nbr, kBinCap = LinkCaps<kV>::bins;
@@ -623,12 +708,9 @@ __global__ __launch_bounds__(kT, 7) void k_links(Bufs B, ParamsDev P, int run) {
   }
   const RunDev &rd = B.runs[run];
   const int ntile = rd.tile1 - rd.tile0;
-  // XCD-aware walk: blocks b with b % 8 == x take the x-th eighth of tiles
-  const int nx = gridDim.x >> 3;
-  const int xcd = blockIdx.x & 7;
-  const int per = (ntile + 7) >> 3;
-  const int lo = xcd * per, hi = min(ntile, lo + per);
-  for (int it = lo + (int)(blockIdx.x >> 3); it < hi; it += nx) {
+  for (int j = (int)(blockIdx.x >> 3);; j += (int)(gridDim.x >> 3)) {
+    const int it = xcd_tile(j);
+    if (it >= ntile) break;
     const int4 tile = B.tiles[rd.tile0 + it];
     const int cnt = tile.w;
     if (cnt == 0) continue;
@@ -710,6 +792,101 @@ __global__ __launch_bounds__(kT, 7) void k_links(Bufs B, ParamsDev P, int run) {
       B.dn[g] = ok ? b.d : -1;
     }
     __syncthreads();
+  }
+}
+
+// The same search by waves, for runs whose rows are sparse (minimum-bias
+// events, peripheral events, single sectors): a wave takes a tile of its own,
+// with the neighbours of 64 hits at a time in its own part of the LDS, and no
+// barrier.  With 46 hits in a row (64 minimum-bias events) a block of 256
+// threads per tile keeps one lane in six busy and waits three times for its
+// slowest wave: 1145 us, against 610 us here.  Bound by instruction issue (216
+// million vector instructions, 65% of the time at four cycles each).
+template <int kNbr, int kBins>
+__global__ __launch_bounds__(256, 5) void k_links_waves(Bufs B, ParamsDev P, int run) {
+  __shared__ float2 s_up_[4][kNbr + 1], s_dn_[4][kNbr + 1];
+  __shared__ uint16_t s_bup_[4][kBins + 1], s_bdn_[4][kBins + 1];
+  __shared__ float s_w[kMaxRows + 1];
+  const int R = P.n_rows;
+  for (int q = 1 + threadIdx.x; q < R - 1; q += blockDim.x) {
+    const float xr = B.row_x[q];
+    const float dxu = B.row_x[q + 1] - xr, dxd = xr - B.row_x[q - 1];
+    s_w[q] = dxd / (dxd + dxu);
+  }
+  for (int q = threadIdx.x; q < 4 * (kNbr + 1); q += blockDim.x)
+    (&s_up_[0][0])[q] = (&s_dn_[0][0])[q] = make_float2(0.0f, 0.0f);  // defined spare entries
+  __syncthreads();
+  const int wid = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+  float2 *const s_up = s_up_[wid], *const s_dn = s_dn_[wid];
+  uint16_t *const s_bup = s_bup_[wid], *const s_bdn = s_bdn_[wid];
+  const RunDev &rd = B.runs[run];
+  const int ntile = rd.tile1 - rd.tile0;
+  for (int j = (int)(blockIdx.x >> 3) * 4 + wid;; j += (int)(gridDim.x >> 3) * 4) {
+    const int it = xcd_tile(j);
+    if (it >= ntile) break;
+    const int4 tile = B.tiles[rd.tile0 + it];
+    const int u = __builtin_amdgcn_readfirstlane(tile.x), r = __builtin_amdgcn_readfirstlane(tile.y);
+    const int g0 = __builtin_amdgcn_readfirstlane(tile.z), cnt = __builtin_amdgcn_readfirstlane(tile.w);
+    if (cnt == 0) continue;
+    if (r < 1 || r > R - 2) {
+      for (int i = lane; i < cnt; i += 64) {
+        B.up[g0 + i] = -1;
+        B.dn[g0 + i] = -1;
+      }
+      continue;
+    }
+    const RowTab *rtu = B.rowtab + (int64_t)u * (R + 1);
+    const RowTab tu = rtu[r + 1], td = rtu[r - 1];
+    const float xr = B.row_x[r];
+    const float dxu = B.row_x[r + 1] - xr;
+    const float dxd = xr - B.row_x[r - 1];
+    const float luy = P.wy * dxu, luz = P.wz * dxu, ldy = P.wy * dxd, ldz = P.wz * dxd;
+    const float w = s_w[r];
+    // 64 hits at a time, each lot with the neighbours of its own z range
+    for (int i = lane; i - lane < cnt; i += 64) {
+      const bool mine = i < cnt;
+      const float2 h = mine ? B.yz[g0 + i] : make_float2(0.0f, 0.0f);
+      const int o = ordered_int(h.y);
+      const float zlo = from_ordered(wave_min_dpp(mine ? o : 0x7FFFFFFF));
+      const float zhi = from_ordered(wave_max_dpp(mine ? o : (int)0x80000000));
+      const float tpad = 1e-3f + 1e-6f * fmaxf(fabsf(zlo), fabsf(zhi));
+      const int ublo = __builtin_amdgcn_readfirstlane(zbin(tu, zlo - luz - tpad));
+      const int ubhi = __builtin_amdgcn_readfirstlane(zbin(tu, zhi + luz + tpad));
+      const int dblo = __builtin_amdgcn_readfirstlane(zbin(td, zlo - ldz - tpad));
+      const int dbhi = __builtin_amdgcn_readfirstlane(zbin(td, zhi + ldz + tpad));
+      const int ua = B.binbeg[tu.bin0 + ublo], ue_ = B.binbeg[tu.bin0 + ubhi + 1];
+      const int da = B.binbeg[td.bin0 + dblo], de_ = B.binbeg[td.bin0 + dbhi + 1];
+      const bool lds = (ue_ - ua) <= kNbr && (de_ - da) <= kNbr && (ubhi - ublo + 2) <= kBins &&
+                       (dbhi - dblo + 2) <= kBins;
+      wave_lds_order();  // the neighbours of the lot before have been read
+      if (lds) {
+        for (int q = lane; q < ue_ - ua; q += 64) s_up[q] = B.yz[ua + q];
+        for (int q = lane; q < de_ - da; q += 64) s_dn[q] = B.yz[da + q];
+        for (int q = lane; q <= ubhi - ublo + 1; q += 64)
+          s_bup[q] = (uint16_t)(B.binbeg[tu.bin0 + ublo + q] - ua);
+        for (int q = lane; q <= dbhi - dblo + 1; q += 64)
+          s_bdn[q] = (uint16_t)(B.binbeg[td.bin0 + dblo + q] - da);
+      }
+      wave_lds_order();
+      if (mine) {
+        const float pad = 1e-3f + 1e-6f * fabsf(h.y);
+        const int bu0 = zbin(tu, h.y - luz - pad), bu1 = zbin(tu, h.y + luz + pad);
+        const int bd0 = zbin(td, h.y - ldz - pad), bd1 = zbin(td, h.y + ldz + pad);
+        LinkBest b;
+        if (lds) {
+          const int ub = ua + s_bup[bu0 - ublo], ue = ua + s_bup[bu1 + 1 - ublo];
+          const int db = da + s_bdn[bd0 - dblo], de = da + s_bdn[bd1 + 1 - dblo];
+          b = link_hit_lds(B, h, luy, luz, ldy, ldz, w, ub, ue, db, de, s_up, s_dn, ua, da);
+        } else {
+          const int ub = B.binbeg[tu.bin0 + bu0], ue = B.binbeg[tu.bin0 + bu1 + 1];
+          const int db = B.binbeg[td.bin0 + bd0], de = B.binbeg[td.bin0 + bd1 + 1];
+          b = link_all_pairs<false>(B, h, luy, luz, ldy, ldz, w, ub, ue, db, de, nullptr, nullptr, 0, 0);
+        }
+        const bool ok = b.u >= 0 && b.c2 <= P.link_chi2;
+        B.up[g0 + i] = ok ? b.u : -1;
+        B.dn[g0 + i] = ok ? b.d : -1;
+      }
+    }
   }
 }
 
@@ -1355,10 +1532,12 @@ hipError_t launch_grid(const Bufs &B, const ParamsDev &P, int run, const RunHost
   if (nu > 0) {
     // dense rows (time frames): the staged sort, one 1024-thread block per CU
     const int64_t rows = (int64_t)nu * (R + 1);
-    if (h.dense)
+    if (h.rows == kRowsDense)
       k_rowsort<1024, true><<<grid_for(rows, 1, 16384), 1024, 0, s>>>(B, run, R);
-    else
+    else if (h.rows == kRowsLong)
       k_rowsort<kBlock, false><<<grid_for(rows, 1, 16384), kBlock, 0, s>>>(B, run, R);
+    else
+      k_rowsort_waves<<<grid_for(rows, 16, 4096), 1024, 0, s>>>(B, run, R);
   }
   return hipGetLastError();
 }
@@ -1370,6 +1549,10 @@ hipError_t launch_links(const Bufs &B, const ParamsDev &P, int run, const RunHos
     int g = grid_for(nt, 1, 256 * (P.link_blocks_per_cu > 0 ? P.link_blocks_per_cu : 32));
     g = (g + 7) & ~7;  // a multiple of the 8 XCDs
     const int tile = link_tile_of(P);
+    if (h.rows == kRowsSparse && P.link_tile <= 0 && P.link_stage == 0) {
+      k_links_waves<256, 128><<<(grid_for(nt, 4, 256 * 32) + 7) & ~7, 256, 0, s>>>(B, P, run);
+      return hipGetLastError();
+    }
 #define TPCCA_LINKS(V, T) k_links<V, T><<<g, T, 0, s>>>(B, P, run)
     switch (P.link_stage * 4 + (tile == 128 ? 0 : tile == 512 ? 2 : 1)) {
       case 8: TPCCA_LINKS(2, 128); break;

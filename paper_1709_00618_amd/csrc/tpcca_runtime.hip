@@ -123,7 +123,7 @@ static void drop_graphs(tpcca_ctx *c) {
 
 static bool same_capacities(const RunHost &a, const RunHost &b) {
   return a.u1 == b.u1 && a.c1 == b.c1 && a.cl1 == b.cl1 && a.bin1 == b.bin1 && a.trk_cap == b.trk_cap &&
-         a.tile1 == b.tile1 && a.dense == b.dense;
+         a.tile1 == b.tile1 && a.rows == b.rows;
 }
 
 static int dev_err(tpcca_ctx *c, hipError_t e, const char *what) {
@@ -342,7 +342,7 @@ static RunHost make_run(tpcca_ctx *c, int u0, int u1) {
   h.trk_cap = (int32_t)(L.trk_base + trk_cap_of(L.n, c->P.min_chain) - h.trk0);
   h.tile0 = c->units[u0].tile_base;
   h.tile1 = (int32_t)(L.tile_base + tile_cap_of(L.n, c->R, link_tile_of(c->P)));
-  h.dense = (int64_t)(h.cl1 - h.cl0) / ((int64_t)(u1 - u0) * (c->R + 1)) >= 1024 ? 1 : 0;
+  h.rows = row_class(u1 - u0, h.cl1 - h.cl0, c->R);
   return h;
 }
 
@@ -1357,7 +1357,7 @@ extern "C" int tpcca_run_batch_noalloc(const tpcca_geometry_t *geo, const tpcca_
   h.trk_cap = (int32_t)trk_total;
   h.tile0 = 0;
   h.tile1 = (int32_t)tiles_total;
-  h.dense = n_total / ((int64_t)U * (R + 1)) >= 1024 ? 1 : 0;
+  h.rows = row_class(U, n_total, R);
   RunDev &rd = H.runs[0];
   rd.u0 = h.u0;
   rd.u1 = h.u1;

@@ -95,3 +95,42 @@ def test_fit_forms_against_the_oracle(tpcca, torch_cuda, row_x, tracks, sectors)
             assert w["fit_steps"] == sum(r.work["propagations"] for r in refs)
             assert w["fit_tests"] == sum(r.work["tests"] for r in refs)
             assert w["fit_updates"] == sum(r.work["updates"] for r in refs)
+
+
+def _unit_of_rows(row_x, counts, seed, z_of=None):
+    """A unit with counts[r] hits in row r, at random y and z (z_of: rows whose
+    hits lie at almost one z, so that a lot of 64 hits has them all as neighbours)."""
+    rng = np.random.default_rng(seed)
+    parts, rows = [], []
+    for r, k in enumerate(counts):
+        z = 10.0 + rng.uniform(-0.05, 0.05, k) if z_of and r in z_of else rng.uniform(0.0, 250.0, k)
+        parts.append(np.stack([np.full(k, row_x[r]), rng.uniform(-0.13, 0.13, k) * row_x[r], z, np.ones(k)], axis=1))
+        rows.append(np.full(k, r, np.uint8))
+    cl, row = np.concatenate(parts).astype(np.float32), np.concatenate(rows)
+    o = rng.permutation(cl.shape[0])
+    return np.ascontiguousarray(cl[o]), np.ascontiguousarray(row[o])
+
+
+# hits in every row: the classes of mean row length (lines at 96, 300 and 1024), then
+# single rows around a wave's lanes, a tile and the longest row that a wave sorts
+@pytest.mark.parametrize("base", [2, 94, 97, 298, 303])
+def test_rows_around_the_wave_and_block_forms(tpcca, row_x, base):
+    """Row sort and neighbour search, by waves and by blocks, at row lengths around
+    their edges, two units in one run."""
+    R = len(row_x)
+    counts = np.full(R, base)
+    if base == 2:
+        special = [0, 1, 63, 64, 65, 127, 128, 129, 255, 256, 257, 511, 512, 513, 700]
+        counts[10:10 + 2 * len(special):2] = special
+        counts[11:11 + 2 * len(special):2] = special[::-1]
+        counts[60:63], counts[70:73], counts[80:83] = (255, 300, 256), (257, 20, 258), (600, 64, 40)
+    units = [_unit_of_rows(row_x, counts, 1, {60, 61, 62, 70, 71, 72, 80, 81, 82}),
+             _unit_of_rows(row_x, np.full(R, base), 2)]
+    with tpcca.Context(row_x) as ctx:
+        for s, (cl, row) in enumerate(units):
+            ctx.load_sector(0, s, cl, row)
+        ctx.run_all(0, -1)
+        ctx.sync()
+        for s, (cl, row) in enumerate(units):
+            print(f"base {base}: unit {s}, {cl.shape[0]} hits", flush=True)
+            _parity.compare_unit_stagewise(ctx, 0, s, cl, row, oracle.run_sector(cl, row, row_x))
