@@ -32,6 +32,7 @@ inline int row_class(int64_t units, int64_t hits, int R) {
 
 hipError_t launch_fill_i32(int32_t *p, int64_t n, int32_t v, hipStream_t s);
 hipError_t launch_fill_u64(unsigned long long *p, int64_t n, unsigned long long v, hipStream_t s);
+hipError_t launch_write_run(const Bufs &B, int run, const RunDev &d, hipStream_t s);
 hipError_t launch_grid(const Bufs &B, const ParamsDev &P, int run, const RunHost &h, hipStream_t s);
 hipError_t launch_links(const Bufs &B, const ParamsDev &P, int run, const RunHost &h, hipStream_t s);
 hipError_t launch_clean(const Bufs &B, const ParamsDev &P, int run, const RunHost &h, hipStream_t s);

@@ -52,6 +52,10 @@ __global__ void k_fill_u64(unsigned long long *p, int64_t n, unsigned long long 
     p[i] = v;
 }
 
+// A run's table entry, passed as the kernel's argument: nothing to wait for,
+// where a copy from the caller's stack has to end before the caller goes on.
+__global__ void k_write_run(RunDev *dst, RunDev d) { *dst = d; }
+
 // Reset of a run's per-unit tables and device counters.
 __global__ void k_run_reset(Bufs B, int run, int R) {
   RunDev &rd = B.runs[run];
@@ -1518,6 +1522,11 @@ hipError_t launch_fill_u64(unsigned long long *p, int64_t n, unsigned long long 
 hipError_t launch_scan_tiles(int64_t *sums, int64_t n, hipStream_t s) {
   if (n < 0) return hipSuccess;
   k_scan_tiles<<<1, 1024, 0, s>>>(sums, n);
+  return hipGetLastError();
+}
+
+hipError_t launch_write_run(const Bufs &B, int run, const RunDev &d, hipStream_t s) {
+  k_write_run<<<1, 1, 0, s>>>(B.runs + run, d);
   return hipGetLastError();
 }
 

@@ -60,6 +60,9 @@ struct tpcca_ctx {
   std::map<std::pair<int, int>, int> index;
   int64_t n_total = 0, bins_total = 0, trk_total = 0, tiles_total = 0, in_used = 0;
   bool tables_dirty = true;
+  char *tables_pin = nullptr;  // pinned copy of the tables under way to the device
+  size_t tables_pin_bytes = 0;
+  hipEvent_t tables_sent = nullptr;  // its copies have been made
   std::vector<int> pending_runs;  // runs launched since the last sync
 
   // device buffers
@@ -293,16 +296,34 @@ static int ensure_work(tpcca_ctx *c, int64_t n_cl, int64_t n_units, int64_t n_bi
   return TPCCA_OK;
 }
 
+// The unit and chunk tables go through a pinned copy of their own, so that the
+// caller need not wait until they have arrived.
 static int upload_tables(tpcca_ctx *c) {
   if (!c->tables_dirty) return TPCCA_OK;
-  if (!c->units.empty())
-    HIPCHK(c, hipMemcpyAsync(c->units_d.p, c->units.data(), c->units.size() * sizeof(UnitDev),
-                             hipMemcpyHostToDevice, c->stream));
-  if (!c->chunks.empty())
-    HIPCHK(c, hipMemcpyAsync(c->chunks_d.p, c->chunks.data(), c->chunks.size() * sizeof(Chunk),
-                             hipMemcpyHostToDevice, c->stream));
-  // host vectors may be modified by later loads before the copy runs
-  HIPCHK(c, hipStreamSynchronize(c->stream));
+  const size_t nu = c->units.size() * sizeof(UnitDev), nc = c->chunks.size() * sizeof(Chunk);
+  if (nu + nc == 0) return TPCCA_OK;
+  if (c->tables_sent) HIPCHK(c, hipEventSynchronize(c->tables_sent));  // the copies before have read it
+  if (nu + nc > c->tables_pin_bytes) {
+    std::lock_guard<std::recursive_mutex> lock(tpcca::device_ops_lock());
+    if (!c->tables_sent) HIPCHK(c, hipEventCreateWithFlags(&c->tables_sent, hipEventDisableTiming));
+    if (c->tables_pin) hipHostFree(c->tables_pin);
+    c->tables_pin = nullptr;
+    c->tables_pin_bytes = 0;
+    const size_t bytes = (nu + nc + (nu + nc) / 4 + 4095) & ~(size_t)4095;
+    void *p = nullptr;
+    HIPCHK(c, hipHostMalloc(&p, bytes, hipHostMallocDefault));
+    c->tables_pin = static_cast<char *>(p);
+    c->tables_pin_bytes = bytes;
+  }
+  if (nu) {
+    std::memcpy(c->tables_pin, c->units.data(), nu);
+    HIPCHK(c, hipMemcpyAsync(c->units_d.p, c->tables_pin, nu, hipMemcpyHostToDevice, c->stream));
+  }
+  if (nc) {
+    std::memcpy(c->tables_pin + nu, c->chunks.data(), nc);
+    HIPCHK(c, hipMemcpyAsync(c->chunks_d.p, c->tables_pin + nu, nc, hipMemcpyHostToDevice, c->stream));
+  }
+  HIPCHK(c, hipEventRecord(c->tables_sent, c->stream));
   c->tables_dirty = false;
   return TPCCA_OK;
 }
@@ -322,8 +343,7 @@ static int write_run(tpcca_ctx *c, int run) {
   d.trk_cap = h.trk_cap;
   d.tile0 = h.tile0;
   d.tile1 = h.tile1;
-  // pageable source: the copy completes before return
-  RCCHK(copy_sync(c, ptr<RunDev>(c->runs_d) + run, &d, sizeof(d), hipMemcpyHostToDevice));
+  HIPCHK(c, launch_write_run(c->B, run, d, c->stream));
   return TPCCA_OK;
 }
 
@@ -447,11 +467,16 @@ static int stage_call(tpcca_ctx *c, int slot, int sector, int stage) {
 }
 
 static int check_errors(tpcca_ctx *c) {
+  // the runs launched since the last call, one copy for those that follow
+  // one another
+  std::vector<RunDev> rd(c->pending_runs.size());
+  tpcca::RangeCopy copy(hipMemcpyDeviceToHost, c->stream);
+  for (size_t k = 0; k < rd.size(); ++k)
+    HIPCHK(c, copy.add(&rd[k], ptr<RunDev>(c->runs_d) + c->pending_runs[k], sizeof(RunDev)));
+  HIPCHK(c, copy.flush());
   HIPCHK(c, hipStreamSynchronize(c->stream));
   int rc = TPCCA_OK;
-  for (int run : c->pending_runs) {
-    RunDev d;
-    RCCHK(copy_sync(c, &d, ptr<RunDev>(c->runs_d) + run, sizeof(d), hipMemcpyDeviceToHost));
+  for (const RunDev &d : rd) {
     if (d.err & 2) {
       c->last_error = "internal error: inconsistent fit order";
       rc = TPCCA_EDEVICE;
@@ -684,6 +709,8 @@ int tpcca_destroy(tpcca_ctx_t *c) {
     if (b->p) hipFree(b->p);
   for (int k = 0; k < 7; ++k)
     if (c->ev[k]) hipEventDestroy(c->ev[k]);
+  if (c->tables_pin) hipHostFree(c->tables_pin);
+  if (c->tables_sent) hipEventDestroy(c->tables_sent);
   if (c->own_stream && c->stream) hipStreamDestroy(c->stream);
   delete c;
   return TPCCA_OK;
@@ -1118,18 +1145,21 @@ int tpcca_get_batch_results(tpcca_ctx_t *c, tpcca_unit_result_t *units, tpcca_tr
     return TPCCA_ECAPACITY;
   // batch-relative offsets
   int64_t to = 0, ho = 0;
+  tpcca::RangeCopy ct(hipMemcpyDeviceToHost, c->stream), ch(hipMemcpyDeviceToHost, c->stream);
   for (int u = 0; u < U; ++u) {
-    if (tracks && ur[u].n_tracks)
-      HIPCHK(c, hipMemcpyAsync(tracks + to, ptr<tpcca_track_t>(c->tracks) + ur[u].track_begin,
-                               sizeof(tpcca_track_t) * ur[u].n_tracks, hipMemcpyDeviceToHost, c->stream));
-    if (hits && ur[u].n_track_hits)
-      HIPCHK(c, hipMemcpyAsync(hits + ho, ptr<int32_t>(c->hits_out) + ur[u].hit_begin,
-                               sizeof(int32_t) * ur[u].n_track_hits, hipMemcpyDeviceToHost, c->stream));
+    if (tracks)
+      HIPCHK(c, ct.add(tracks + to, ptr<tpcca_track_t>(c->tracks) + ur[u].track_begin,
+                       sizeof(tpcca_track_t) * ur[u].n_tracks));
+    if (hits)
+      HIPCHK(c, ch.add(hits + ho, ptr<int32_t>(c->hits_out) + ur[u].hit_begin,
+                       sizeof(int32_t) * ur[u].n_track_hits));
     ur[u].track_begin = to;
     ur[u].hit_begin = ho;
     to += ur[u].n_tracks;
     ho += ur[u].n_track_hits;
   }
+  HIPCHK(c, ct.flush());
+  HIPCHK(c, ch.flush());
   if (assignment && c->n_total)
     HIPCHK(c, hipMemcpyAsync(assignment, c->assign.p, sizeof(int32_t) * c->n_total, hipMemcpyDeviceToHost,
                              c->stream));
@@ -1659,6 +1689,20 @@ int tpcca_get_finals(tpcca_ctx_t *c, int32_t slot, tpcca_final_t *out, int32_t c
   RCCHK(p2_ready(c));
   if (!n_out) return TPCCA_EINVAL;
   const int nf = c->p2c.n_final;
+  if (c->p2_slot_value.size() == 1 && c->p2_slot_value[0] == slot) {
+    // every final track is the slot's: straight to the caller
+    *n_out = nf;
+    if (n_hits_out) *n_hits_out = c->p2c.n_final_hits;
+    if (cap < nf || (hits && hits_cap < c->p2c.n_final_hits)) return TPCCA_ECAPACITY;
+    if (out && nf)
+      HIPCHK(c, hipMemcpyAsync(out, c->p2finals.p, sizeof(tpcca_final_t) * nf, hipMemcpyDeviceToHost, c->stream));
+    if (hits && c->p2c.n_final_hits)
+      HIPCHK(c, hipMemcpyAsync(hits, c->p2final_hits.p, sizeof(int32_t) * c->p2c.n_final_hits,
+                               hipMemcpyDeviceToHost, c->stream));
+    HIPCHK(c, hipStreamSynchronize(c->stream));
+    for (int f = 0; out && f < nf; ++f) out[f].slot = slot;  // the lists already lie one after the other
+    return TPCCA_OK;
+  }
   std::vector<tpcca_final_t> all(nf);
   if (nf) RCCHK(copy_sync(c, all.data(), c->p2finals.p, sizeof(tpcca_final_t) * nf, hipMemcpyDeviceToHost));
   std::vector<int> mine;
@@ -1672,16 +1716,17 @@ int tpcca_get_finals(tpcca_ctx_t *c, int32_t slot, tpcca_final_t *out, int32_t c
   if (n_hits_out) *n_hits_out = nh;
   if (cap < (int32_t)mine.size() || (hits && hits_cap < nh)) return TPCCA_ECAPACITY;
   int64_t off = 0;
+  tpcca::RangeCopy ch(hipMemcpyDeviceToHost, c->stream);  // the lists of a unit's finals follow one another
   for (size_t k = 0; k < mine.size(); ++k) {
     tpcca_final_t o = all[mine[k]];
-    if (hits && o.n_hits)
-      HIPCHK(c, hipMemcpyAsync(hits + off, ptr<int32_t>(c->p2final_hits) + o.hit_begin, sizeof(int32_t) * o.n_hits,
-                               hipMemcpyDeviceToHost, c->stream));
+    if (hits)
+      HIPCHK(c, ch.add(hits + off, ptr<int32_t>(c->p2final_hits) + o.hit_begin, sizeof(int32_t) * o.n_hits));
     o.slot = slot;
     o.hit_begin = off;
     off += o.n_hits;
     if (out) out[k] = o;
   }
+  HIPCHK(c, ch.flush());
   HIPCHK(c, hipStreamSynchronize(c->stream));
   return TPCCA_OK;
 }

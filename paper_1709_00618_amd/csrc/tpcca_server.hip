@@ -192,21 +192,25 @@ void lane_main(tpcca_server *S, int lane) {
     bn.resize(U);
     bbegin.resize(U);
     int64_t off = 0;
-    for (int i = 0; i < U && rc == TPCCA_OK; ++i) {
-      Request &r = *items[i].req;
-      const int u = items[i].unit;
-      bslot[i] = i;  // distinct slot per unit inside the batch
-      bsector[i] = r.sector[u];
-      bn[i] = r.n[u];
-      bbegin[i] = off;
-      if (r.n[u] > 0) {
-        if (hipMemcpyAsync(d_cl + off, r.tf.cl + r.begin[u], sizeof(float4) * r.n[u],
-                           hipMemcpyHostToDevice, st) != hipSuccess ||
-            hipMemcpyAsync(d_row + off, r.tf.row + r.begin[u], r.n[u], hipMemcpyHostToDevice, st) !=
-                hipSuccess)
-          rc = TPCCA_EDEVICE;
+    {
+      tpcca::RangeCopy ccl(hipMemcpyHostToDevice, st), crow(hipMemcpyHostToDevice, st);
+      hipError_t e = hipSuccess;
+      for (int i = 0; i < U && rc == TPCCA_OK && e == hipSuccess; ++i) {
+        Request &r = *items[i].req;
+        const int u = items[i].unit;
+        bslot[i] = i;  // distinct slot per unit inside the batch
+        bsector[i] = r.sector[u];
+        bn[i] = r.n[u];
+        bbegin[i] = off;
+        e = ccl.add(d_cl + off, r.tf.cl + r.begin[u], sizeof(float4) * r.n[u]);
+        if (e == hipSuccess) e = crow.add(d_row + off, r.tf.row + r.begin[u], r.n[u]);
+        off += r.n[u];
+        if (i + 1 == U || items[i + 1].req != items[i].req) {  // the next frame is another buffer
+          if (e == hipSuccess) e = ccl.flush();
+          if (e == hipSuccess) e = crow.flush();
+        }
       }
-      off += r.n[u];
+      if (e != hipSuccess) rc = TPCCA_EDEVICE;
     }
     if (rc == TPCCA_OK) {
       tpcca_batch_t b{};
@@ -256,20 +260,22 @@ void lane_main(tpcca_server *S, int lane) {
         ok[i] = 1;
       }
     }
+    tpcca::RangeCopy ct(hipMemcpyDeviceToHost, st), ch(hipMemcpyDeviceToHost, st), ca(hipMemcpyDeviceToHost, st);
     for (int i = 0; i < U && rc == TPCCA_OK; ++i) {
-      if (!ok[i]) continue;
       Request &r = *items[i].req;
       const int u = items[i].unit;
       hipError_t e = hipSuccess;
-      if (ur[i].n_tracks && r.tf.tracks)
-        e = hipMemcpyAsync(r.tf.tracks + tpos[i], dr.tracks + ur[i].track_begin,
-                           sizeof(tpcca_track_t) * ur[i].n_tracks, hipMemcpyDeviceToHost, st);
-      if (e == hipSuccess && ur[i].n_track_hits && r.tf.hits)
-        e = hipMemcpyAsync(r.tf.hits + hpos[i], dr.hits + ur[i].hit_begin,
-                           sizeof(int32_t) * ur[i].n_track_hits, hipMemcpyDeviceToHost, st);
-      if (e == hipSuccess && r.n[u] && r.tf.assignment)
-        e = hipMemcpyAsync(r.tf.assignment + r.cl_offset[u], dr.assignment + ur[i].cluster_begin,
-                           sizeof(int32_t) * r.n[u], hipMemcpyDeviceToHost, st);
+      if (ok[i] && r.tf.tracks)
+        e = ct.add(r.tf.tracks + tpos[i], dr.tracks + ur[i].track_begin, sizeof(tpcca_track_t) * ur[i].n_tracks);
+      if (e == hipSuccess && ok[i] && r.tf.hits)
+        e = ch.add(r.tf.hits + hpos[i], dr.hits + ur[i].hit_begin, sizeof(int32_t) * ur[i].n_track_hits);
+      if (e == hipSuccess && ok[i] && r.tf.assignment)
+        e = ca.add(r.tf.assignment + r.cl_offset[u], dr.assignment + ur[i].cluster_begin, sizeof(int32_t) * r.n[u]);
+      if (i + 1 == U || items[i + 1].req != items[i].req) {  // the next frame has buffers of its own
+        if (e == hipSuccess) e = ct.flush();
+        if (e == hipSuccess) e = ch.flush();
+        if (e == hipSuccess) e = ca.flush();
+      }
       if (e != hipSuccess) {
         rc = TPCCA_EDEVICE;
         fail_text = std::string("result copy: ") + hipGetErrorString(e);

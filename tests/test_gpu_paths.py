@@ -134,3 +134,49 @@ def test_rows_around_the_wave_and_block_forms(tpcca, row_x, base):
         for s, (cl, row) in enumerate(units):
             print(f"base {base}: unit {s}, {cl.shape[0]} hits", flush=True)
             _parity.compare_unit_stagewise(ctx, 0, s, cl, row, oracle.run_sector(cl, row, row_x))
+
+
+def test_results_of_units_in_any_order(tpcca, torch_cuda, row_x):
+    """Copies of units that lie one after the other are joined: units loaded in
+    another order (reversed, two slots in turn, one left out, one empty) give the
+    same results per unit and per slot, from the batch, the finals and a server."""
+    from paper_1709_00618_amd import serving
+    b = tpcgen.minbias_batch(seed=9, n_events=2)
+    some = [u for u in range(72) if u % 36 < 12 and u != 5]
+    turn = [u for s in range(12) for u in (s, 36 + s) if u != 5]
+
+    def run(order):
+        units = np.array([b.units[u] for u in order], np.int64)
+        units[order.index(7), 1] = 0
+        with tpcca.Context(row_x) as ctx:
+            ctx.run_batch(b.cl, b.row, units, device=False)
+            res, tracks, hits, asg = ctx.get_batch_results()
+            per, off = {}, 0
+            for k, u in enumerate(order):
+                t0, h0, nt, nh = (int(res[k][f]) for f in ("track_begin", "hit_begin", "n_tracks", "n_track_hits"))
+                n = int(units[k, 1])
+                per[u] = (tracks[t0:t0 + nt].tobytes(), hits[h0:h0 + nh].tobytes(), asg[off:off + n].tobytes())
+                off += n
+            ctx.phase2()
+            finals = [tuple(a.tobytes() for a in ctx.get_finals(slot)) for slot in (0, 1)]
+        frame = [k for k, u in enumerate(order) if u < 36]
+        f = serving.Frame(b.cl, b.row, units[frame])
+        o = serving.Outputs(f.n_clusters, f.n_units)
+        with serving.Server(row_x, n_streams=1, budget_bytes=2 << 30) as srv:
+            rid = srv.submit(f, o)
+            assert srv.wait(rid, 100).status == tpcca.OK
+            served = {}
+            for k, (t, h, a) in zip(frame, serving.unit_results(f, o)):
+                served[order[k]] = (t.tobytes(), h.tobytes(), a.tobytes())
+            srv.release(rid)
+        return per, finals, served
+
+    per, finals, served = run(some)
+    assert sum(len(p[0]) > 0 for p in per.values()) > 15 and len(finals[0][0]) and len(finals[1][0])
+    for u, p in served.items():
+        assert p == per[u]
+    for order in (some[::-1], turn, turn[::-1]):
+        p2, f2, s2 = run(order)
+        assert p2 == per and s2 == served
+        if order is turn:
+            assert f2 == finals
