@@ -28,7 +28,7 @@ CACHE = os.path.join(HERE, "tuning_cache.json")
 SPACE = {
     "fit_block": [0, 64, 256],
     "fit_blocks_per_cu": [0, 6, 4, 8, 12],
-    "fit_min_waves": [0, 5],
+    "fit_min_waves": [0],
     "fit_pool": [64, 128, 32],
     "link_stage": [0, 1, 2],
     "link_tile": [0, 128, 512],

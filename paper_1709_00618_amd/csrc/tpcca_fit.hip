@@ -123,11 +123,19 @@ __device__ __forceinline__ void pool_claim(const ParamsDev &P, Pool &p, int32_t 
   }
 }
 
+// 16 B at p: a row's grid description, or a sorted hit (8 B) and the next.
+__device__ __forceinline__ int4 load16(const void *p) {
+  int4 v;
+  __builtin_memcpy(&v, __builtin_assume_aligned(p, 8), 16);
+  return v;
+}
+
 // Nearest hit (dy^2 + dz^2, ties to the lower ID) of the row described by t
 // inside the prediction window; -1 if none; its coordinates are returned
 // in bc.
 // The state's z is relative to zr; the bins are looked up around the absolute
 // prediction zr + z with a margin that covers its rounding.
+template <int kQ>
 __device__ __forceinline__ int kf_search(const Bufs &B, const ParamsDev &P, const RowTab &t,
                                          const KState &s, float zr, unsigned int &cands, float2 &bc) {
   // with cluster variances the roots' arguments are in kf_sqrt's range
@@ -143,26 +151,29 @@ __device__ __forceinline__ int kf_search(const Bufs &B, const ParamsDev &P, cons
   int best = -1;
   float bd2 = __builtin_inff();
   bool tie = false;
-  // candidates in ascending sorted index, loaded kQ at a time (independent
-  // loads in flight, the last ones repeated past the end); a second hit at
-  // exactly the best distance (rare) is only noted
-  constexpr int kQ = 4;
+  // candidates in ascending sorted index, kQ at a time in 16-B loads of two
+  // (independent loads in flight, the last ones repeated past the end); a
+  // second hit at exactly the best distance (rare) is only noted.  The state
+  // machine waits less with eight (a frame of 33 M clusters: 8.4 ms, 8.9 with
+  // four, 9.4 with sixteen); a lone wave's loops do not.
   for (int i0 = b; i0 < e; i0 += kQ) {
-    float2 c[kQ];
+    int4 c[kQ / 2];
 #pragma unroll
-    for (int q = 0; q < kQ; ++q) c[q] = B.yz[min(i0 + q, e - 1)];
+    for (int q = 0; q < kQ / 2; ++q) c[q] = load16(B.yz + min(i0 + 2 * q, e - 1));
 #pragma unroll
     for (int q = 0; q < kQ; ++q) {
-      const float dy = c[q].x - s.p[0];
-      const float dz = (c[q].y - zr) - s.p[1];
+      const float cy = __int_as_float(q & 1 ? c[q / 2].z : c[q / 2].x);
+      const float cz = __int_as_float(q & 1 ? c[q / 2].w : c[q / 2].y);
+      const float dy = cy - s.p[0];
+      const float dz = (cz - zr) - s.p[1];
       const float d2 = __builtin_fmaf(dy, dy, dz * dz);
       const bool in = (i0 + q < e) & (fabsf(dy) <= wy) & (fabsf(dz) <= wz);
       const bool lt = in & (d2 < bd2);
       tie = !lt & (tie | (in & (d2 == bd2)));
       bd2 = lt ? d2 : bd2;
       best = lt ? i0 + q : best;
-      bc.x = lt ? c[q].x : bc.x;
-      bc.y = lt ? c[q].y : bc.y;
+      bc.x = lt ? cy : bc.x;
+      bc.y = lt ? cz : bc.y;
     }
   }
   if (tie && best >= 0) {  // equal distances are decided by the lower cluster ID
@@ -227,6 +238,12 @@ struct Aux {
   }
 };
 
+// Tracklets that a wave reads ahead, and that end before it writes their claims.
+// Both wait for chains of dependent reads (a start four, a claim three): one
+// tracklet at a time they took 1.2 of 10.0 ms on a frame of 33 M clusters,
+// where a wave's 64 lanes end one after the other.
+constexpr int kSeeds = 16, kDone = 8;
+
 // What both forms of the kernel share of a block: LDS and the work totals
 // (row steps, candidates, tests, updates, iterations), which go out with one
 // global atomic per counter and block, and with none from blocks without work
@@ -235,6 +252,10 @@ template <int kBlk>
 struct FitBlock {
   Aux<kBlk> aux;
   Slots<kBlk> slot;
+  int2 head[kBlk];         // the tracklet's first hit (row << 24 | cluster ID), its chain's length
+  int4 seed[kBlk / 64][3][kSeeds];  // tracklets read ahead
+  int2 seed_head[kBlk / 64][kSeeds];
+  int4 done[kBlk / 64][kDone];      // tracklets that ended (record, hits, chi2, unit's first cluster)
   float rx[kMaxRows + 1];  // the row positions
   unsigned int steps, cands, tests, updates, iters;
 };
@@ -244,12 +265,6 @@ struct Work {
   unsigned int steps = 0, cands = 0, tests = 0, updates = 0, iters = 0;
 };
 
-// 16 B at p: a row's grid description, or a sorted hit (8 B) and the next.
-__device__ __forceinline__ int4 load16(const void *p) {
-  int4 v;
-  __builtin_memcpy(&v, __builtin_assume_aligned(p, 8), 16);
-  return v;
-}
 __device__ __forceinline__ RowTab row_bins(int4 v) {
   RowTab t;
   t.nb = v.x;
@@ -270,31 +285,57 @@ struct Trk {
   int4 v;
 };
 
-// Tracklet at position i of the processing order: seed state at the chain's
-// first hit (its row in r, its slot in s0), the chain's second hit.
-__device__ __forceinline__ void fit_seed(const Bufs &B, const ParamsDev &P, const float *rx, int pos, Trk &k,
-                                         KState &st, int32_t &s0) {
-  k.t = B.kf_order[pos];
-  const int g0 = B.trk_start[k.t];
-  const int u = B.trk_unit[k.t];
-  k.ucl = B.units[u].cl_begin;
-  k.rb = u * (P.n_rows + 1);
+// What a tracklet's start takes from memory: its unit, the chain's first hit
+// (position, slot, cluster ID) and the next two, the chain's length and the
+// seed's direction.
+struct Seed {
+  int t, u, ucl, s0, hn, hx;
+  float y, z, sn, p3;
+  float2 next;
+  int2 head;  // cluster ID, chain length
+};
+
+// The tracklet at position pos of the processing order.
+__device__ __forceinline__ Seed fit_read(const Bufs &B, const ParamsDev &P, const float *rx, int pos) {
+  Seed a;
+  a.t = B.kf_order[pos];
+  const int g0 = B.trk_start[a.t];
+  a.u = B.trk_unit[a.t];
+  a.ucl = B.units[a.u].cl_begin;
   const int2 ci = B.cinfo[g0];
-  k.hn = B.upc[g0];
-  k.r = B.srow[g0];
+  a.hn = B.upc[g0];
+  const int r = B.srow[g0];
+  a.head = make_int2(B.sid[g0], ci.y);
   const float2 h0 = B.yz[g0], hL = B.yz[ci.x];
-  k.v = load16(B.yz + k.hn);
-  k.hx = B.upc[k.hn];
-  const float x0 = rx[k.r], xL = rx[k.r + ci.y - 1];
+  a.next = B.yz[a.hn];
+  a.hx = B.upc[a.hn];
+  const float x0 = rx[r], xL = rx[r + ci.y - 1];
   const float dxs = xL - x0;
   const float ty = (hL.x - h0.x) / dxs;
-  const float sn = ty / sqrtf(__builtin_fmaf(ty, ty, 1.0f));
+  a.sn = ty / sqrtf(__builtin_fmaf(ty, ty, 1.0f));
   const float tz = (hL.y - h0.y) / dxs;
-  k.zr = h0.y;
-  st.p[0] = h0.x;
-  st.p[1] = h0.y - k.zr;
-  st.p[2] = sn;
-  st.p[3] = tz * sqrtf(__builtin_fmaf(-sn, sn, 1.0f));
+  a.y = h0.x;
+  a.z = h0.y;
+  a.p3 = tz * sqrtf(__builtin_fmaf(-a.sn, a.sn, 1.0f));
+  a.s0 = slot_enc(g0, a.ucl, r);
+  return a;
+}
+
+// Its fit, about to step to the chain's second hit.
+template <int kBlk>
+__device__ __forceinline__ void fit_start(const ParamsDev &P, FitBlock<kBlk> &S, const Seed &a, Trk &k, KState &st) {
+  k.t = a.t;
+  k.rb = a.u * (P.n_rows + 1);
+  k.ucl = a.ucl;
+  k.r = slot_row(a.s0) + 1;
+  k.hn = a.hn;
+  k.hx = a.hx;
+  k.zr = a.z;
+  k.v = make_int4(__float_as_int(a.next.x), __float_as_int(a.next.y), 0, 0);
+  st.p[0] = a.y;
+  st.p[1] = a.z - k.zr;
+  st.p[2] = a.sn;
+  st.p[3] = a.p3;
   st.p[4] = 0.0f;
 #pragma unroll
   for (int q = 0; q < 15; ++q) st.C[q] = 0.0f;
@@ -303,13 +344,15 @@ __device__ __forceinline__ void fit_seed(const Bufs &B, const ParamsDev &P, cons
   st.C[5] = P.c22;
   st.C[9] = P.c33;
   st.C[14] = P.c44;
-  st.x = x0;
-  s0 = slot_enc(g0, k.ucl, k.r);
+  st.x = S.rx[k.r - 1];
+  S.slot.at(0) = a.s0;
+  S.head[threadIdx.x] = make_int2((int)((uint32_t)(k.r - 1) << 24) | a.head.x, a.head.y);
 }
 
-__device__ __forceinline__ void fit_failed(const Bufs &B, int t) {
-  const int g0 = B.trk_start[t];
-  kf_fail(B, t, B.sid[g0], B.cinfo[g0].y);
+template <int kBlk>
+__device__ __forceinline__ void fit_failed(const Bufs &B, const FitBlock<kBlk> &S, int t) {
+  const int2 hd = S.head[threadIdx.x];
+  kf_fail(B, t, hd.x & 0xFFFFFF, hd.y);
 }
 
 // The end of pass 1 (n1 hits): its last (partial) slot group goes to memory
@@ -345,18 +388,18 @@ template <int kBlk>
 __device__ __forceinline__ bool fit_done(const Bufs &B, const ParamsDev &P, FitBlock<kBlk> &S, const Trk &k, int n1,
                                          int nh, float chi2, int32_t *slots) {
   tpcca_tracklet_t &o = B.trk[k.t];
-  const int g0 = B.trk_start[k.t];
+  const int2 hd = S.head[threadIdx.x];
   // the last partial group of pass-2 slots (one that does not share pass-1
   // slots) goes to memory
   const int jl = nh - 1;
   if (nh > n1 && (jl & kGM) != kGM && (jl & ~kGM) >= n1) S.slot.flush(slots, jl);
   const KState a = S.aux.load();
-  o.start_id = B.sid[g0];
-  o.n_chain = B.cinfo[g0].y;
+  o.start_id = hd.x & 0xFFFFFF;
+  o.n_chain = hd.y;
   o.n_hits = nh;
   o.n_pass1 = n1;
   o.ndf = 2 * nh - 5;
-  o.row_ref = nh > n1 ? slot_row(S.slot.at(jl)) : (int)B.srow[g0];
+  o.row_ref = nh > n1 ? slot_row(S.slot.at(jl)) : slot_row(hd.x);
   o.x_ref = a.x;
   o.chi2 = chi2;
 #pragma unroll
@@ -367,26 +410,55 @@ __device__ __forceinline__ bool fit_done(const Bufs &B, const ParamsDev &P, FitB
   return nh >= P.min_hits;
 }
 
-// The selection's claims of the tracklets `fin` that ended: the wave writes
-// the claim key of each into the owner word of its hits (one tracklet at a
-// time, hit slots read by all lanes).
-__device__ __forceinline__ void fit_claims(const Bufs &B, unsigned long long fin, const Trk &k, int nh, float chi2,
-                                           int Rs, int lane) {
-  if (!fin) return;
+// The selection's claims of the wave's n tracklets that ended: the claim key
+// of each goes into the owner words of its hits, four tracklets' slots in
+// flight.
+template <int kBlk>
+__device__ __forceinline__ void fit_claim(const Bufs &B, const FitBlock<kBlk> &S, int n, int Rs) {
+  static_assert(kMaxRows < 4 * 64, "a lane takes four of a tracklet's hits");
+  const int lane = threadIdx.x & 63;
+  const int4 *done = S.done[threadIdx.x >> 6];
+  wave_lds_order();
   // the hit slots were written by other lanes of this wave
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-  while (fin) {
-    const int src = __builtin_ctzll(fin);
-    fin &= fin - 1;
-    // wave-uniform values of the source lane (scalar registers)
-    const int tt = __builtin_amdgcn_readlane(k.t, src);
-    const int nn = __builtin_amdgcn_readlane(nh, src);
-    const int uc = __builtin_amdgcn_readlane(k.ucl, src);
-    const float c2 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(chi2), src));
-    const unsigned long long kk = claim_key(nn, c2, B.sid[B.trk_start[tt]]);
-    const int32_t *hh = B.trk_hits + (int64_t)tt * Rs;
-    for (int j = lane; j < nn; j += 64) atomicMax(&B.owner[slot_hit(hh[j], uc)], kk);
+  for (int e = 0; e < n; e += 4) {
+    int4 d[4], h[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      d[q] = done[min(e + q, n - 1)];
+      if (4 * lane < slot_row(d[q].w)) h[q] = reinterpret_cast<const int4 *>(B.trk_hits + (int64_t)d[q].x * Rs)[lane];
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int nh = e + q < n ? slot_row(d[q].w) : 0, j = 4 * lane;
+      const unsigned long long key = claim_key(nh, __int_as_float(d[q].z), d[q].w & 0xFFFFFF);
+      if (j < nh) atomicMax(&B.owner[slot_hit(h[q].x, d[q].y)], key);
+      if (j + 1 < nh) atomicMax(&B.owner[slot_hit(h[q].y, d[q].y)], key);
+      if (j + 2 < nh) atomicMax(&B.owner[slot_hit(h[q].z, d[q].y)], key);
+      if (j + 3 < nh) atomicMax(&B.owner[slot_hit(h[q].w, d[q].y)], key);
+    }
+  }
+  wave_lds_order();  // the entries are free again
+}
+
+// Notes the lanes' tracklets that ended (fin) for the claims, n of them so far.
+template <int kBlk>
+__device__ __forceinline__ void fit_ended(const Bufs &B, FitBlock<kBlk> &S, bool fin, const Trk &k, int nh, float chi2,
+                                          int Rs, int &n) {
+  for (unsigned long long left = __ballot(fin); left;) {
+    const int lane = threadIdx.x & 63, at = n + __popcll(left & ((1ull << lane) - 1));
+    const bool put = (left >> lane & 1) && at < kDone;
+    if (put)  // rows are as many as hits or more: a hit count has a row's size
+      S.done[threadIdx.x >> 6][at] = make_int4(k.t, k.ucl, __float_as_int(chi2),
+                                               (int)((uint32_t)nh << 24) | (S.head[threadIdx.x].x & 0xFFFFFF));
+    const unsigned long long gone = __ballot(put);
+    n += __popcll(gone);
+    left &= ~gone;
+    if (n == kDone) {
+      fit_claim(B, S, n, Rs);
+      n = 0;
+    }
   }
 }
 
@@ -413,7 +485,7 @@ __device__ __forceinline__ void few_follow(const Bufs &B, const ParamsDev &P, Fi
     const bool ok = kf_step(P, st, S.rx[r]);
     int h = -1;
     float2 c = make_float2(0.0f, 0.0f);
-    if (ok) h = kf_search(B, P, row_bins(v), st, k.zr, w.cands, c);
+    if (ok) h = kf_search<4>(B, P, row_bins(v), st, k.zr, w.cands, c);
     v = load16(B.rowtab + k.rb + max(r + dir, 0));
     w.tests += h >= 0 ? 1u : 0u;
     KMeas m;
@@ -444,10 +516,9 @@ __device__ __forceinline__ bool few_tracklet(const Bufs &B, const ParamsDev &P, 
                                              int &nh, float &chi2, Work &w) {
   KState st;
   int32_t sv;
-  fit_seed(B, P, S.rx, pos, k, st, sv);
+  fit_start(P, S, fit_read(B, P, S.rx, pos), k, st);
   int32_t *slots = B.trk_hits + (int64_t)k.t * slot_stride(P.n_rows);
-  S.slot.at(0) = sv;
-  const int r0 = k.r;
+  const int r0 = k.r - 1;
   nh = 1;
   bool ok, go;
   KMeas m;
@@ -502,14 +573,14 @@ __device__ __forceinline__ bool few_tracklet(const Bufs &B, const ParamsDev &P, 
       return fit_done(B, P, S, k, n1, nh, chi2, slots);
     }
   }
-  fit_failed(B, k.t);
+  fit_failed(B, S, k.t);
   return false;
 }
 
 template <int kBlk>
 __device__ __forceinline__ void fit_few(const Bufs &B, const ParamsDev &P, RunDev &rd, FitBlock<kBlk> &S, Work &w) {
   const int lane = threadIdx.x & 63;
-  int lo, hi;
+  int lo, hi, ended = 0;
   few_share(rd.n_trk, lo, hi);
   for (int i = lo; i < hi; i += 64) {
     Trk k;
@@ -517,7 +588,7 @@ __device__ __forceinline__ void fit_few(const Bufs &B, const ParamsDev &P, RunDe
     float chi2 = 0.0f;
     Work mine;
     const bool fin = i + lane < hi && few_tracklet(B, P, S, rd.trk0 + i + lane, k, nh, chi2, mine);
-    if (P.kf_claims) fit_claims(B, __ballot(fin), k, nh, chi2, slot_stride(P.n_rows), lane);
+    if (P.kf_claims) fit_ended(B, S, fin, k, nh, chi2, slot_stride(P.n_rows), ended);
     // totals of the wave; it stepped at least as often as its longest tracklet
     w.iters += (unsigned int)wave_max_dpp((int)mine.steps);
     w.steps += wave_sum(mine.steps);
@@ -525,6 +596,7 @@ __device__ __forceinline__ void fit_few(const Bufs &B, const ParamsDev &P, RunDe
     w.tests += wave_sum(mine.tests);
     w.updates += wave_sum(mine.updates);
   }
+  if (ended) fit_claim(B, S, ended, slot_stride(P.n_rows));
 }
 
 // -------------------------------------------------- many: state machine ---
@@ -539,7 +611,9 @@ template <int kBlk>
 __device__ __forceinline__ void fit_many(const Bufs &B, const ParamsDev &P, RunDev &rd, FitBlock<kBlk> &S, Work &w) {
   const int R = P.n_rows, Rs = slot_stride(R);
   const int n_trk = rd.n_trk;
-  const int tid = threadIdx.x, lane = tid & 63;
+  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  int ahead = 0, taken = 0;  // tracklets read ahead and not started, those started before them
+  int ended = 0;             // tracklets whose claims are not written
   Pool pool = pool_start(P, n_trk);
   bool told = false;  // the drain's start was recorded
   int state = kFree;
@@ -551,21 +625,41 @@ __device__ __forceinline__ void fit_many(const Bufs &B, const ParamsDev &P, RunD
   for (;;) {
     const unsigned long long idle = __ballot(state == kFree);
     if (idle) {
-      while (pool.next == pool.end && !pool.exhausted)
-        pool_claim(P, pool, rd.kf_next, n_trk, __popcll(idle), lane);
-      if (pool.next < pool.end) {
-        const int take = min(__popcll(idle), pool.end - pool.next);
+      if (ahead == 0) {
+        // the next tracklets, read by as many lanes at a time
+        while (pool.next == pool.end && !pool.exhausted)
+          pool_claim(P, pool, rd.kf_next, n_trk, __popcll(idle), lane);
+        ahead = min(kSeeds, pool.end - pool.next);
+        wave_lds_order();
+        if (lane < ahead) {
+          const Seed a = fit_read(B, P, S.rx, rd.trk0 + pool.next + lane);
+          S.seed[wid][0][lane] = make_int4(a.t, a.u, a.ucl, a.s0);
+          S.seed[wid][1][lane] = make_int4(a.hn, a.hx, __float_as_int(a.next.x), __float_as_int(a.next.y));
+          S.seed[wid][2][lane] = make_int4(__float_as_int(a.y), __float_as_int(a.z), __float_as_int(a.sn),
+                                           __float_as_int(a.p3));
+          S.seed_head[wid][lane] = a.head;
+        }
+        wave_lds_order();
+        pool.next += ahead;
+        taken = 0;
+      }
+      if (ahead) {
+        const int take = min(__popcll(idle), ahead);
         const int rank = __popcll(idle & ((1ull << lane) - 1));
         if (state == kFree && rank < take) {
-          int32_t s0;
-          fit_seed(B, P, S.rx, rd.trk0 + pool.next + rank, k, st, s0);
-          S.slot.at(0) = s0;
+          const int4 a = S.seed[wid][0][taken + rank], b = S.seed[wid][1][taken + rank],
+                     c = S.seed[wid][2][taken + rank];
+          fit_start(P, S,
+                    Seed{a.x, a.y, a.z, a.w, b.x, b.y, __int_as_float(c.x), __int_as_float(c.y), __int_as_float(c.z),
+                         __int_as_float(c.w), make_float2(__int_as_float(b.z), __int_as_float(b.w)),
+                         S.seed_head[wid][taken + rank]},
+                    k, st);
           nh = 1;
           n1 = 0;
-          ++k.r;
           state = kLink;
         }
-        pool.next += take;
+        taken += take;
+        ahead -= take;
       } else {
         if (idle == ~0ull) break;
         if (!told) {
@@ -587,7 +681,7 @@ __device__ __forceinline__ void fit_many(const Bufs &B, const ParamsDev &P, RunD
     bool upd = given & ok;
     const bool search = prop && !given && ok;
     if (search) {
-      h = kf_search(B, P, row_bins(k.v), st, k.zr, w.cands, c);
+      h = kf_search<8>(B, P, row_bins(k.v), st, k.zr, w.cands, c);
       upd = h >= 0;
     }
     w.tests += __popcll(__ballot(search && upd));
@@ -644,7 +738,7 @@ __device__ __forceinline__ void fit_many(const Bufs &B, const ParamsDev &P, RunD
         state = kSearch;
       }
     } else if (given) {
-      fit_failed(B, k.t);
+      fit_failed(B, S, k.t);
       state = kFree;
     } else if (state >= kSearch) {
       if (search && ++state < P.max_miss) {
@@ -663,12 +757,13 @@ __device__ __forceinline__ void fit_many(const Bufs &B, const ParamsDev &P, RunD
         state = kFree;
       }
     }
-    if (P.kf_claims) fit_claims(B, __ballot(fin), k, nh, chi2, Rs, lane);
+    if (P.kf_claims) fit_ended(B, S, fin, k, nh, chi2, Rs, ended);
   }
+  if (ended) fit_claim(B, S, ended, Rs);
 }
 
-template <int kMinWaves, int kBlk>
-__global__ __launch_bounds__(kBlk, kMinWaves) void k_kf(Bufs B, ParamsDev P, int run) {
+template <int kBlk>
+__global__ __launch_bounds__(kBlk, 4) void k_kf(Bufs B, ParamsDev P, int run) {
   __shared__ FitBlock<kBlk> S;
   RunDev &rd = B.runs[run];
   if (threadIdx.x == 0) S.steps = S.cands = S.tests = S.updates = S.iters = 0;
@@ -705,18 +800,12 @@ __global__ __launch_bounds__(kBlk, kMinWaves) void k_kf(Bufs B, ParamsDev P, int
 
 // ------------------------------------------------------------ launchers ---
 // Compute units and resident fit blocks per CU of the current device, for
-// each register variant and block size; queried once per device
-// (contexts on several host threads launch concurrently, hence the lock).
+// each block size; queried once per device (contexts on several host threads
+// launch concurrently, hence the lock).
 struct KfOccupancy {
   int cus = 1;
-  int per[2][3] = {};  // [register variant][64, 128, 256 threads]
+  int per[3] = {};  // 64, 128, 256 threads
 };
-
-template <int kBlk>
-static void kf_occ(KfOccupancy &o, int b) {
-  (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&o.per[0][b], k_kf<4, kBlk>, kBlk, 0);
-  (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&o.per[1][b], k_kf<5, kBlk>, kBlk, 0);
-}
 
 static const KfOccupancy &kf_occupancy() {
   static std::mutex mu;
@@ -729,12 +818,11 @@ static const KfOccupancy &kf_occupancy() {
   KfOccupancy o;
   int cus = 0;
   (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-  kf_occ<64>(o, 0);
-  kf_occ<128>(o, 1);
-  kf_occ<256>(o, 2);
+  (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&o.per[0], k_kf<64>, 64, 0);
+  (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&o.per[1], k_kf<128>, 128, 0);
+  (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&o.per[2], k_kf<256>, 256, 0);
   o.cus = std::max(1, cus);
-  for (auto &v : o.per)
-    for (int &b : v) b = std::max(1, b);
+  for (int &b : o.per) b = std::max(1, b);
   return cache.emplace(dev, o).first->second;
 }
 
@@ -746,28 +834,22 @@ hipError_t launch_kf(const Bufs &B, const ParamsDev &P, int run, const RunHost &
   if (P.kf_rows > 0) return launch_kf_rows(B, P, run, h, s);
   if (h.trk_cap <= 0) return hipSuccess;
   // at most the resident capacity of the chip, and enough waves to give few
-  // tracklets a wave each.  register budgets: 4 (default) or 5 resident waves
-  // per SIMD (5 spills 40 B: time frame of 33 M clusters 10.3 against 9.8 ms);
-  // block sizes 64, 128 (default) or 256 threads
-  const int v = P.kf_min_waves >= 5 ? 1 : 0;
+  // tracklets a wave each; block sizes 64, 128 (default) or 256 threads.  Four
+  // waves share a SIMD, by registers (128) and by LDS.
   const int blk = kf_block_of(P);
   const int bi = blk == 64 ? 0 : blk == 256 ? 2 : 1;
   const KfOccupancy &o = kf_occupancy();
-  const int per = o.per[v][bi];
+  const int per = o.per[bi];
   const int64_t cap = (int64_t)o.cus * (P.kf_blocks_per_cu > 0 ? std::min(P.kf_blocks_per_cu, per) : per);
   const int64_t need = std::max<int64_t>(((int64_t)h.trk_cap + blk - 1) / blk,
                                          std::min<int64_t>(h.trk_cap, kFewWaves) * 64 / blk + 1);
   const int g = (int)std::min(cap, need);
-#define TPCCA_KF(W, T) k_kf<W, T><<<g, T, 0, s>>>(B, P, run)
-  switch (v * 3 + bi) {
-    case 0: TPCCA_KF(4, 64); break;
-    case 2: TPCCA_KF(4, 256); break;
-    case 3: TPCCA_KF(5, 64); break;
-    case 4: TPCCA_KF(5, 128); break;
-    case 5: TPCCA_KF(5, 256); break;
-    default: TPCCA_KF(4, 128); break;
-  }
-#undef TPCCA_KF
+  if (blk == 64)
+    k_kf<64><<<g, 64, 0, s>>>(B, P, run);
+  else if (blk == 256)
+    k_kf<256><<<g, 256, 0, s>>>(B, P, run);
+  else
+    k_kf<128><<<g, 128, 0, s>>>(B, P, run);
   return hipGetLastError();
 }
 

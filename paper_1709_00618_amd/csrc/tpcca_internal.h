@@ -92,7 +92,7 @@ struct ParamsDev {
   int32_t kf_pool;
   int32_t kf_blocks_per_cu;
   int32_t link_blocks_per_cu;
-  int32_t kf_min_waves;
+  int32_t kf_min_waves;  // kept for tpcca_get_tuning
   int32_t kf_claims;   // 1: the fit writes the selection's claims, 0: a kernel of its own
   int32_t kf_xcd;      // 1: the fit's order is cut into one slice per XCD
   int32_t link_stage;  // staging capacity variant of the neighbour kernel (0..2)

@@ -62,7 +62,8 @@ FIT_FORMS = [
     dict(),                                     # the loops: one tracklet per wave up to 2048, then several lanes
     dict(fit_xcd_slices=1),                     # the state machine (never the loops), claims from eight counters
     dict(fit_block=64, fit_blocks_per_cu=1),    # 256 waves: a wave's share exceeds its 64 lanes
-    dict(fit_block=256, fit_min_waves=5),       # the 5-wave register budget
+    dict(fit_block=256, fit_min_waves=5),       # the largest block
+    dict(fit_pool=200, fit_xcd_slices=1),       # claims longer than the tracklets read ahead
     dict(fit_claims=0),                         # claims in a kernel of their own
 ]
 
@@ -70,8 +71,8 @@ FIT_FORMS = [
 @pytest.mark.parametrize("tracks, sectors", [(12, 1), (700, 3), (8000, 4)])
 def test_fit_forms_against_the_oracle(tpcca, torch_cuda, row_x, tracks, sectors):
     """Both forms of the fit kernel (loops for few tracklets, state machine for
-    many) at tracklet counts below and above a wave each, with every register
-    budget and block size, against the oracle: tracklets, tracks, assignment."""
+    many) at tracklet counts below and above a wave each, with every block size,
+    against the oracle: tracklets, tracks, assignment."""
     torch = torch_cuda
     ev = tpcgen.central_event(seed=5, n_tracks=tracks, keep_truth=False)
     parts = [ev.unit(u) for u in range(sectors)]
