@@ -827,10 +827,6 @@ static const KfOccupancy &kf_occupancy() {
 }
 
 hipError_t launch_kf(const Bufs &B, const ParamsDev &P, int run, const RunHost &h, hipStream_t s) {
-  // the claim words of the selection start at zero (the fit may write them
-  // as its tracklets end)
-  hipError_t e = launch_fill_u64(B.owner + h.cl0, h.cl1 - h.cl0, 0ull, s);
-  if (e != hipSuccess) return e;
   if (P.kf_rows > 0) return launch_kf_rows(B, P, run, h, s);
   if (h.trk_cap <= 0) return hipSuccess;
   // at most the resident capacity of the chip, and enough waves to give few

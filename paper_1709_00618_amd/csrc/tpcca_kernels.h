@@ -13,6 +13,7 @@ struct RunHost {
   int32_t trk0, trk_cap;
   int32_t tile0, tile1;
   int32_t rows;  // how full the pad rows of the run's units are: a RowClass
+  int32_t lds_unit;  // the run's units have at most this many hits (0: more), see unit_class
 };
 
 // By mean hits in a pad row: which kernels sort the rows and search the
@@ -28,6 +29,15 @@ enum RowClass { kRowsSparse, kRowsShort, kRowsLong, kRowsDense };
 inline int row_class(int64_t units, int64_t hits, int R) {
   const int64_t rows = units * (R + 1);
   return hits < rows * 96 ? kRowsSparse : hits < rows * 300 ? kRowsShort : hits < rows * 1024 ? kRowsLong : kRowsDense;
+}
+
+// Units of up to kLdsUnit hits (133 of a CU's 160 KB) have their chains built in
+// LDS, one block per unit (kLdsUnitSmall: several blocks share a CU).  The second
+// kernel sums the tracklet counts of all units before its own, which bounds the
+// units.
+constexpr int kLdsUnitSmall = 8192, kLdsUnit = 40960, kLdsUnits = 4096;
+inline int unit_class(int64_t units, int64_t largest) {
+  return units > kLdsUnits ? 0 : largest <= kLdsUnitSmall ? kLdsUnitSmall : largest <= kLdsUnit ? kLdsUnit : 0;
 }
 
 hipError_t launch_fill_i32(int32_t *p, int64_t n, int32_t v, hipStream_t s);

@@ -898,7 +898,10 @@ __global__ __launch_bounds__(256, 5) void k_links_waves(Bufs B, ParamsDev P, int
 // Fig. 1b: keep a link only if its partner links back; a hit with an up
 // link and no down link starts a chain.  Each chunk lists its start hits in
 // its own region of a staging array (an LDS counter, no global atomics) and
-// stores their count for the scan that compacts the lists.
+// stores their count for the scan that compacts the lists.  What the later
+// stages expect cleared or empty (start flags, claim words, assignment) is
+// written here as well: fills of their own took four launches, 19 us of a
+// sector's 650.
 __global__ __launch_bounds__(kBlock) void k_clean(Bufs B, int run) {
   __shared__ int cnt;
   const RunDev &rd = B.runs[run];
@@ -932,6 +935,10 @@ __global__ __launch_bounds__(kBlock) void k_clean(Bufs B, int run) {
       const int dc = (ld[q] >= 0 && pd[q] == g) ? ld[q] : -1;
       B.upc[g] = uc;
       B.dnc[g] = dc;
+      B.flag[g] = 0;
+      B.sval[g] = 0;
+      B.assign[g] = -1;
+      B.owner[g] = 0ull;
       if (uc >= 0 && dc < 0) stage[cb + atomicAdd(&cnt, 1)] = make_int2(g, U.cl_begin + B.sid[g]);
     }
     __syncthreads();
@@ -978,6 +985,150 @@ __global__ __launch_bounds__(kBlock) void k_chain(Bufs B, ParamsDev P, int run) 
       // 2: a long chain, fitted in the first part of the processing order
       B.sval[g] = (P.kf_split > 0 && P.kf_bands == 0 && n >= P.kf_split) ? 2 : 1;
     }
+  }
+}
+
+// Units that fit a CU's LDS: a block per unit takes the unit's links there
+// (16-bit indices), lists its start hits and follows the chains at LDS instead
+// of L2 latency, and marks the tracklets in two bit maps, by start hit and by
+// start ID, from which the second kernel reads all ranks.  The path below takes
+// ten launches with scans between them for the same.  Bound by a serial chain
+// (159 LDS reads, 15 us of a peripheral event); before and after, both kernels
+// against the ten: peripheral event 71 -> 24 us, central event 109 -> 45, 64
+// minimum-bias events 480 -> 185.
+template <int kCap>
+struct ChainUnit {
+  uint16_t up[kCap];
+  uint16_t start[kCap / 2];  // a chain has two hits or more
+  uint32_t by_hit[kCap / 32], by_id[kCap / 32];
+  int starts, tracklets;
+};
+
+// The unit's bit maps, kept in its flag words (two or more hits, two or more
+// words for each 32).
+__device__ __forceinline__ uint32_t *unit_maps(const Bufs &B, const UnitDev &U) {
+  return reinterpret_cast<uint32_t *>(B.flag + U.cl_begin);
+}
+
+template <int kCap, int kT>
+__global__ __launch_bounds__(kT) void k_chain_units(Bufs B, ParamsDev P, int run, int R) {
+  __shared__ ChainUnit<kCap> S;
+  const RunDev &rd = B.runs[run];
+  const int lane = threadIdx.x & 63;
+  for (int w = blockIdx.x; w < rd.u1 - rd.u0; w += gridDim.x) {
+    const UnitDev U = B.units[rd.u0 + w];
+    const int n = min(U.n, kCap), words = (n + 31) >> 5;
+    const int32_t *upc = B.upc + U.cl_begin, *dnc = B.dnc + U.cl_begin;
+    if (threadIdx.x == 0) S.starts = S.tracklets = 0;
+    for (int i = threadIdx.x; i < words; i += kT) S.by_hit[i] = S.by_id[i] = 0u;
+    __syncthreads();
+    constexpr int kQ = 4;  // hits of a thread in flight
+    for (int i0 = 0; i0 < n; i0 += kQ * kT) {
+      int a[kQ], b[kQ];
+#pragma unroll
+      for (int q = 0; q < kQ; ++q) {
+        const int i = i0 + q * kT + (int)threadIdx.x;
+        a[q] = i < n ? upc[i] : -1;
+        b[q] = i < n ? dnc[i] : -1;
+      }
+#pragma unroll
+      for (int q = 0; q < kQ; ++q) {
+        const int i = i0 + q * kT + (int)threadIdx.x;
+        if (i < n) S.up[i] = a[q] >= 0 ? (uint16_t)(a[q] - U.cl_begin) : 0xFFFFu;
+        const bool is = a[q] >= 0 && b[q] < 0;
+        const unsigned long long m = __ballot(is);
+        int at = 0;
+        if (lane == 0 && m) at = atomicAdd(&S.starts, __popcll(m));
+        at = __builtin_amdgcn_readfirstlane(at) + __popcll(m & ((1ull << lane) - 1));
+        if (is && at < kCap / 2) S.start[at] = (uint16_t)i;
+      }
+    }
+    __syncthreads();
+    for (int k = threadIdx.x; k < S.starts; k += kT) {
+      const int g = S.start[k];
+      int len = 1, last = g;
+      unsigned int nx = S.up[g];
+      for (int s = 0; nx != 0xFFFFu && s < P.n_rows; ++s) {
+        ++len;
+        last = (int)nx;
+        nx = S.up[nx];
+      }
+      if (len >= P.min_chain) {
+        const int id = B.sid[U.cl_begin + g];
+        B.cinfo[U.cl_begin + g] = make_int2(U.cl_begin + last, len);
+        atomicOr(&S.by_hit[g >> 5], 1u << (g & 31));
+        atomicOr(&S.by_id[id >> 5], 1u << (id & 31));
+        atomicAdd(&S.tracklets, 1);
+      }
+    }
+    __syncthreads();
+    if (S.tracklets) {
+      uint32_t *maps = unit_maps(B, U);
+      for (int i = threadIdx.x; i < words; i += kT) {
+        maps[i] = S.by_hit[i];
+        maps[words + i] = S.by_id[i];
+      }
+    }
+    if (threadIdx.x == 0) B.row_fill[(int64_t)rd.u0 * (R + 1) + w] = S.tracklets;
+    __syncthreads();
+  }
+}
+
+// The tracklets of a unit: numbered by unit and start ID, fitted in the order
+// of unit and start hit.
+template <int kCap, int kT>
+__global__ __launch_bounds__(kT) void k_rank_units(Bufs B, int run, int R) {
+  constexpr int kWords = kCap / 32;
+  __shared__ uint32_t by_hit[kWords], by_id[kWords];
+  __shared__ uint16_t hit_rank[kWords], id_rank[kWords];
+  __shared__ int lds[kT / 64 + 1];
+  RunDev &rd = B.runs[run];
+  const int nu = rd.u1 - rd.u0;
+  const int32_t *cnt = B.row_fill + (int64_t)rd.u0 * (R + 1);
+  for (int w = blockIdx.x; w < nu; w += gridDim.x) {
+    int before = 0;
+    for (int v = threadIdx.x; v < w; v += kT) before += cnt[v];
+    int t0;
+    block_exclusive_scan<int>(before, lds, &t0);
+    t0 += rd.trk0;
+    const int mine = cnt[w];
+    if (threadIdx.x == 0) {
+      B.unit_tbegin[rd.u0 + w] = t0;
+      if (w == nu - 1) rd.n_trk = t0 - rd.trk0 + mine;
+    }
+    if (mine == 0) continue;
+    const UnitDev U = B.units[rd.u0 + w];
+    const int words = (min(U.n, kCap) + 31) >> 5;
+    const uint32_t *maps = unit_maps(B, U);
+    for (int map = 0; map < 2; ++map) {
+      uint32_t *bits = map ? by_id : by_hit;
+      uint16_t *rank = map ? id_rank : hit_rank;
+      int carry = 0;
+      for (int i0 = 0; i0 < words; i0 += kT) {
+        const int i = i0 + (int)threadIdx.x;
+        const uint32_t m = i < words ? maps[map * words + i] : 0u;
+        int tot;
+        const int ex = block_exclusive_scan<int>(__popc(m), lds, &tot);
+        if (i < words) {
+          bits[i] = m;
+          rank[i] = (uint16_t)(carry + ex);
+        }
+        carry += tot;
+      }
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < words; i += kT) {
+      int p = t0 + hit_rank[i];
+      for (uint32_t m = by_hit[i]; m; m &= m - 1) {
+        const int g = U.cl_begin + i * 32 + __builtin_ctz(m);
+        const int id = B.sid[g];
+        const int t = t0 + id_rank[id >> 5] + __popc(by_id[id >> 5] & ((1u << (id & 31)) - 1u));
+        B.kf_order[p++] = t;
+        B.trk_start[t] = g;
+        B.trk_unit[t] = rd.u0 + w;
+      }
+    }
+    __syncthreads();
   }
 }
 
@@ -1392,26 +1543,66 @@ __device__ __forceinline__ int64_t acc_hits(unsigned long long v) {
 }
 
 // Per-unit result table (after the accepted-track scan).
+__device__ __forceinline__ void unit_result(const Bufs &B, const RunDev &rd, int u) {
+  const UnitDev U = B.units[u];
+  const int tb = B.unit_tbegin[u] - rd.trk0;
+  const int te = (u + 1 < rd.u1) ? B.unit_tbegin[u + 1] - rd.trk0 : rd.n_trk;
+  const unsigned long long a = B.accx[tb], b = B.accx[te];
+  tpcca_unit_result_t r;
+  r.slot = U.slot;
+  r.sector = U.sector;
+  r.n_clusters = U.n;
+  r.n_tracklets = te - tb;
+  r.n_tracks = acc_count(b) - acc_count(a);
+  r.n_track_hits = (int32_t)(acc_hits(b) - acc_hits(a));
+  r.cluster_begin = U.cl_begin;
+  r.track_begin = rd.trk0 + acc_count(a);
+  r.hit_begin = rd.cl0 + acc_hits(a);
+  B.unit_res[u] = r;
+}
+
 __global__ void k_unit_results(Bufs B, int run) {
   const RunDev &rd = B.runs[run];
   for (int u = rd.u0 + blockIdx.x * blockDim.x + threadIdx.x; u < rd.u1;
-       u += gridDim.x * blockDim.x) {
-    const UnitDev U = B.units[u];
-    const int tb = B.unit_tbegin[u] - rd.trk0;
-    const int te = (u + 1 < rd.u1) ? B.unit_tbegin[u + 1] - rd.trk0 : rd.n_trk;
-    const unsigned long long a = B.accx[tb], b = B.accx[te];
-    tpcca_unit_result_t r;
-    r.slot = U.slot;
-    r.sector = U.sector;
-    r.n_clusters = U.n;
-    r.n_tracklets = te - tb;
-    r.n_tracks = acc_count(b) - acc_count(a);
-    r.n_track_hits = (int32_t)(acc_hits(b) - acc_hits(a));
-    r.cluster_begin = U.cl_begin;
-    r.track_begin = rd.trk0 + acc_count(a);
-    r.hit_begin = rd.cl0 + acc_hits(a);
-    B.unit_res[u] = r;
+       u += gridDim.x * blockDim.x)
+    unit_result(B, rd, u);
+}
+
+// The three passes of the scan and the result table in one block, for runs of
+// few tracklet slots (a slot for every three clusters: sectors, peripheral
+// events), where three launches cost 14 us and one tracklet in a dozen slots
+// is there.
+constexpr int kAcceptSmall = 65536;
+__global__ __launch_bounds__(1024) void k_accept_small(Bufs B, int run) {
+  __shared__ int64_t lds[1024 / 64 + 1];
+  RunDev &rd = B.runs[run];
+  const int n = rd.n_trk;
+  constexpr int per = 4;
+  int64_t carry = 0;
+  for (int s = 0; s < n; s += per * 1024) {
+    const int i0 = s + (int)threadIdx.x * per;
+    int64_t v[per], loc = 0;
+#pragma unroll
+    for (int q = 0; q < per; ++q) {
+      v[q] = i0 + q < n ? (int64_t)B.accv[i0 + q] : 0;
+      loc += v[q];
+    }
+    int64_t tot;
+    int64_t ex = carry + block_exclusive_scan<int64_t>(loc, lds, &tot);
+#pragma unroll
+    for (int q = 0; q < per; ++q) {
+      if (i0 + q < n) B.accx[i0 + q] = (unsigned long long)ex;
+      ex += v[q];
+    }
+    carry += tot;
   }
+  if (threadIdx.x == 0) {
+    rd.n_acc = acc_count((unsigned long long)carry);
+    rd.n_acc_hits = acc_hits((unsigned long long)carry);
+    B.accx[n] = (unsigned long long)carry;
+  }
+  __syncthreads();
+  for (int u = rd.u0 + (int)threadIdx.x; u < rd.u1; u += 1024) unit_result(B, rd, u);
 }
 
 // Compaction of accepted tracks, a group of kGrp lanes per tracklet:
@@ -1579,14 +1770,19 @@ hipError_t launch_links(const Bufs &B, const ParamsDev &P, int run, const RunHos
   return hipGetLastError();
 }
 
+// The run's list of start hits, from the chunks' lists of the cleaning.
+static void list_starts(const Bufs &B, int run, int nch, hipStream_t s) {
+  k_scan_tiles<<<1, 1024, 0, s>>>(B.scan_tmp, nch);
+  k_starts_compact<<<grid_for(nch, 1, 8192), kBlock, 0, s>>>(B, run);
+}
+
 hipError_t launch_clean(const Bufs &B, const ParamsDev &P, int run, const RunHost &h,
                         hipStream_t s) {
   (void)P;
   const int nch = h.c1 - h.c0;
   if (nch > 0) {
     k_clean<<<grid_for(nch, 1, 8192), kBlock, 0, s>>>(B, run);
-    k_scan_tiles<<<1, 1024, 0, s>>>(B.scan_tmp, nch);
-    k_starts_compact<<<grid_for(nch, 1, 8192), kBlock, 0, s>>>(B, run);
+    if (!h.lds_unit) list_starts(B, run, nch, s);
   }
   return hipGetLastError();
 }
@@ -1594,13 +1790,22 @@ hipError_t launch_clean(const Bufs &B, const ParamsDev &P, int run, const RunHos
 hipError_t launch_chains(const Bufs &B, const ParamsDev &P, int run, const RunHost &h,
                          hipStream_t s) {
   const int nch = h.c1 - h.c0, nu = h.u1 - h.u0;
-  hipError_t e = launch_fill_i32(B.flag + h.cl0, h.cl1 - h.cl0, 0, s);
-  if (e != hipSuccess) return e;
-  // sval is a byte array: clear it as 32-bit words (its range is padded)
-  e = launch_fill_i32(reinterpret_cast<int32_t *>(B.sval + (h.cl0 & ~3)),
-                      ((int64_t)h.cl1 - (h.cl0 & ~3) + 3) / 4, 0, s);
-  if (e != hipSuccess) return e;
+  const bool plain = P.kf_split <= 0 && P.kf_bands <= 0 && P.kf_rows <= 0;  // the order is by unit and start hit
+  if (h.lds_unit && plain && nu > 0) {
+    if (h.lds_unit == kLdsUnitSmall) {
+      k_chain_units<kLdsUnitSmall, 512><<<grid_for(nu, 1, 2048), 512, 0, s>>>(B, P, run, P.n_rows);
+      k_rank_units<kLdsUnitSmall, 256><<<grid_for(nu, 1, 4096), 256, 0, s>>>(B, run, P.n_rows);
+    } else {
+      k_chain_units<kLdsUnit, 1024><<<grid_for(nu, 1, 256), 1024, 0, s>>>(B, P, run, P.n_rows);
+      k_rank_units<kLdsUnit, 1024><<<grid_for(nu, 1, 512), 1024, 0, s>>>(B, run, P.n_rows);
+    }
+    return hipGetLastError();
+  }
   if (nch > 0) {
+    if (h.lds_unit) {  // the cleaning's lists are no longer there: clean again
+      k_clean<<<grid_for(nch, 1, 8192), kBlock, 0, s>>>(B, run);
+      list_starts(B, run, nch, s);
+    }
     k_chain<<<grid_for(h.cl1 - h.cl0, kBlock, 4096), kBlock, 0, s>>>(B, P, run);
     k_flag_sums<<<grid_for(nch, 1, 8192), kBlock, 0, s>>>(B, run);
     k_scan_tiles<<<1, 1024, 0, s>>>(B.scan_tmp, nch);
@@ -1612,7 +1817,7 @@ hipError_t launch_chains(const Bufs &B, const ParamsDev &P, int run, const RunHo
     k_order_apply<<<grid_for(nch, 1, 8192), kBlock, 0, s>>>(B, run, bands ? B.kf_tmp : B.kf_order);
     if (bands) {
       const int64_t nbk = (int64_t)nu * P.kf_bands;
-      e = launch_fill_i32(B.band_tmp, nbk, 0, s);
+      const hipError_t e = launch_fill_i32(B.band_tmp, nbk, 0, s);
       if (e != hipSuccess) return e;
       k_band_count<<<grid_for(h.trk_cap, kBlock, 4096), kBlock, 0, s>>>(B, P, run);
       k_band_scan<<<1, 1024, 0, s>>>(B, P, run);
@@ -1627,9 +1832,6 @@ hipError_t launch_chains(const Bufs &B, const ParamsDev &P, int run, const RunHo
 
 hipError_t launch_select(const Bufs &B, const ParamsDev &P, int run, const RunHost &h,
                          hipStream_t s) {
-  const int64_t n = h.cl1 - h.cl0;
-  hipError_t e = launch_fill_i32(B.assign + h.cl0, n, -1, s);
-  if (e != hipSuccess) return e;
   const int nu = h.u1 - h.u0;
   const int tg = grid_for((int64_t)h.trk_cap, kBlock, 8192);  // thread per tracklet (claims)
   const int gg = grid_for((int64_t)h.trk_cap * kGrp, kBlock, 8192);  // lane group per tracklet
@@ -1637,11 +1839,15 @@ hipError_t launch_select(const Bufs &B, const ParamsDev &P, int run, const RunHo
   if (h.trk_cap > 0) {
     if (!P.kf_claims) k_claim<<<tg, kBlock, 0, s>>>(B, P, run);
     k_won<kWonGrp><<<gg, kBlock, 0, s>>>(B, P, run);
-    k_acc_sums<<<grid_for(tiles, 1, 8192), kBlock, 0, s>>>(B, run);
   }
-  k_acc_tiles<<<1, 1024, 0, s>>>(B, run);
-  if (h.trk_cap > 0) k_acc_apply<<<grid_for(tiles, 1, 8192), kBlock, 0, s>>>(B, run);
-  if (nu > 0) k_unit_results<<<grid_for(nu, 64, 1024), 64, 0, s>>>(B, run);
+  if (h.trk_cap <= kAcceptSmall) {
+    k_accept_small<<<1, 1024, 0, s>>>(B, run);
+  } else {
+    k_acc_sums<<<grid_for(tiles, 1, 8192), kBlock, 0, s>>>(B, run);
+    k_acc_tiles<<<1, 1024, 0, s>>>(B, run);
+    k_acc_apply<<<grid_for(tiles, 1, 8192), kBlock, 0, s>>>(B, run);
+    if (nu > 0) k_unit_results<<<grid_for(nu, 64, 1024), 64, 0, s>>>(B, run);
+  }
   if (h.trk_cap > 0) k_output<<<gg, kBlock, 0, s>>>(B, P, run);
   return hipGetLastError();
 }

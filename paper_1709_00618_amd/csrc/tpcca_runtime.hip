@@ -126,7 +126,7 @@ static void drop_graphs(tpcca_ctx *c) {
 
 static bool same_capacities(const RunHost &a, const RunHost &b) {
   return a.u1 == b.u1 && a.c1 == b.c1 && a.cl1 == b.cl1 && a.bin1 == b.bin1 && a.trk_cap == b.trk_cap &&
-         a.tile1 == b.tile1 && a.rows == b.rows;
+         a.tile1 == b.tile1 && a.rows == b.rows && a.lds_unit == b.lds_unit;
 }
 
 static int dev_err(tpcca_ctx *c, hipError_t e, const char *what) {
@@ -363,6 +363,9 @@ static RunHost make_run(tpcca_ctx *c, int u0, int u1) {
   h.tile0 = c->units[u0].tile_base;
   h.tile1 = (int32_t)(L.tile_base + tile_cap_of(L.n, c->R, link_tile_of(c->P)));
   h.rows = row_class(u1 - u0, h.cl1 - h.cl0, c->R);
+  int32_t largest = 0;
+  for (int u = u0; u < u1; ++u) largest = std::max(largest, c->units[u].n);
+  h.lds_unit = unit_class(u1 - u0, largest);
   return h;
 }
 
@@ -1356,8 +1359,10 @@ extern "C" int tpcca_run_batch_noalloc(const tpcca_geometry_t *geo, const tpcca_
   noalloc_layout(D.tables.data(), R, n_total, U, bins_total, trk_total, n_chunks, H);
   std::memcpy(const_cast<float *>(H.row_x), geo->row_x, sizeof(float) * (size_t)R);
   int64_t cl = 0, bins = 0, trk = 0, tiles = 0, ch = 0;
+  int32_t largest = 0;
   for (int u = 0; u < U; ++u) {
     const int32_t n = bt->n[u];
+    largest = std::max(largest, n);
     UnitDev &V = H.units[u];
     V.cl = reinterpret_cast<const float4 *>(bt->cl + bt->begin[u]);
     V.row = bt->row + bt->begin[u];
@@ -1388,6 +1393,7 @@ extern "C" int tpcca_run_batch_noalloc(const tpcca_geometry_t *geo, const tpcca_
   h.tile0 = 0;
   h.tile1 = (int32_t)tiles_total;
   h.rows = row_class(U, n_total, R);
+  h.lds_unit = unit_class(U, largest);
   RunDev &rd = H.runs[0];
   rd.u0 = h.u0;
   rd.u1 = h.u1;

@@ -181,3 +181,29 @@ def test_results_of_units_in_any_order(tpcca, torch_cuda, row_x):
         assert p2 == per and s2 == served
         if order is turn:
             assert f2 == finals
+
+
+# hits of the largest unit: chains in LDS (up to 8192, up to 40960 hits), else by lists
+@pytest.mark.parametrize("n", [1, 2, 31, 33, 8191, 8192, 8193, 40959, 40960, 40961])
+def test_chains_around_the_lds_unit_sizes(tpcca, torch_cuda, row_x, n):
+    """Tracklet numbers, fit order and results with units at the sizes where the
+    chain kernels change, beside an empty unit, one cluster and a short unit; then
+    with an order knob set between the cleaning and the chains."""
+    big = tpcgen.central_event(seed=8, n_tracks=12500, keep_truth=False)
+    cl, row, _, _, _ = big.unit(4)
+    assert cl.shape[0] > 40961
+    parts = [(np.ascontiguousarray(cl[:k]), np.ascontiguousarray(row[:k])) for k in (700, n, 0, 1)]
+    refs = [oracle.run_sector(c, r, row_x) for c, r in parts]
+    for knobs in ({}, {"fit_long_first": 60}):
+        with tpcca.Context(row_x) as ctx:
+            for s, (c, r) in enumerate(parts):
+                ctx.load_sector(0, s, c, r)
+            ctx.find_links()
+            ctx.clean_links()
+            ctx.set_tuning(**knobs)
+            ctx.build_tracklets()
+            ctx.select_tracks()
+            ctx.sync()
+            for s, (c, r) in enumerate(parts):
+                _parity.compare_unit_stagewise(ctx, 0, s, c, r, refs[s])
+
