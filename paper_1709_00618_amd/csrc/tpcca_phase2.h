@@ -42,7 +42,7 @@ struct P2Counts {
   int32_t n_seg, n_final, n_cand, n_group, n_vtx, n_slots;
   int64_t n_final_hits;
   int64_t n_pairs;               // candidate pairs of the merge
-  int32_t seg_next, fin_next;    // work counters of the per-lane segment and refit kernels
+  int32_t fin_next;              // work counter of the refit kernel
   int32_t pad_[2];
 };
 

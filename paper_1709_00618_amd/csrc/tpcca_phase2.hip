@@ -177,16 +177,29 @@ __global__ __launch_bounds__(1024) void k_p2_seg_index(Bufs B, P2Bufs Q, int R) 
   if (threadIdx.x == 0) {
     Q.seg_begin[Q.n_units] = (int32_t)carry;
     Q.cnt->n_seg = (int32_t)carry;
-    Q.cnt->seg_next = 0;
     Q.cnt->fin_next = 0;
   }
 }
 
 // ---------------------------------------------------------- compression ---
-__device__ __forceinline__ int32_t p2_quant(float v, float q) {
-  const float r = __builtin_rintf(v / q);
+__device__ __forceinline__ int32_t p2_round(float r) {
+  r = __builtin_rintf(r);
   return fabsf(r) < 1073741824.0f ? (int32_t)r : 0;
 }
+
+// Quotients by the two steps with shared reciprocals: exact for steps in the
+// middle of the exponent range, except where the quotient is so small that it
+// rounds to zero either way.
+struct P2Quant {
+  KRecip ry, rz;
+  float qy, qz;
+  bool mid;
+  __device__ __forceinline__ explicit P2Quant(const P2Params &q)
+      : ry(kf_recip(q.qy)), rz(kf_recip(q.qz)), qy(q.qy), qz(q.qz),
+        mid(q.qy >= 0x1p-60f && q.qy <= 0x1p60f && q.qz >= 0x1p-60f && q.qz <= 0x1p60f) {}
+  __device__ __forceinline__ int32_t y(float v) const { return p2_round(mid ? kf_div(v, ry) : v / qy); }
+  __device__ __forceinline__ int32_t z(float v) const { return p2_round(mid ? kf_div(v, rz) : v / qz); }
+};
 
 struct CmpFit {
   KState st;
@@ -208,11 +221,11 @@ struct CmpFit {
     st.C[9] = q.c33;
     st.C[14] = q.c44;
   }
-  __device__ bool predict(const ParamsDev &P, const P2Params &q, const float *row_x, int r, int32_t &py,
+  __device__ bool predict(const ParamsDev &P, const P2Quant &w, const float *row_x, int r, int32_t &py,
                           int32_t &pz) {
     const bool ok = kf_propagate(P, st, row_x[r]);
-    py = p2_quant(st.p[0], q.qy);
-    pz = p2_quant(st.p[1] + zr, q.qz);
+    py = w.y(st.p[0]);
+    pz = w.z(st.p[1] + zr);
     return ok;
   }
   __device__ void take(const ParamsDev &P, const P2Params &q, bool ok, int32_t yq, int32_t zq) {
@@ -275,116 +288,112 @@ __global__ __launch_bounds__(256) void k_p2_hits(Bufs B, P2Bufs Q, int R) {
   }
 }
 
+// Values that a lane collects in LDS before its wave writes them.
+constexpr int kP2Out = 8;
+
 // Per segment: rows of its first and last won hit, inner and outer z, the
 // outer end (the fitted inner state propagated to each won hit's row in
 // ascending order) and the segment's compressed form (record and residuals);
 // clears the pairing words.
-__global__ __launch_bounds__(256) void k_p2_seg_prep(Bufs B, P2Bufs Q, ParamsDev P, P2Params q) {
+//
+// A lane per segment.  The order is by length, so the 64 of a wave end
+// together, and the waves take them in strides.  Blocks are single waves: a
+// lone wave issues an instruction every five cycles and waves that share a
+// CU slow each other, so an event's 300 waves are to spread over the chip.
+// Bound by instruction issue of the serial chain; central event 443 -> 228 us
+// against blocks of 256 with lane by lane replacement, frame of 16 M clusters
+// 754 -> 392.
+__global__ __launch_bounds__(64) void k_p2_seg_prep(Bufs B, P2Bufs Q, ParamsDev P, P2Params q) {
   __shared__ float s_rx[kMaxRows + 1];  // pad-row positions (off the dependent chain)
   for (int i = threadIdx.x; i < P.n_rows; i += blockDim.x) s_rx[i] = B.row_x[i];
   __syncthreads();
+  // residuals under way: eight of each lane go out together, a lane's by eight
+  // lanes (128 B in a row; 16 B at a time they took 226 of 530 us on a frame of
+  // 16 M clusters)
+  __shared__ int4 s_res[64][kP2Out + 1];
+  __shared__ int64_t s_h0[64];
+  __shared__ int s_nh[64];
+  const int lane = threadIdx.x;
   const int n = Q.cnt->n_seg;
-  const int lane = threadIdx.x & 63;
-  const unsigned long long below = (1ull << lane) - 1;
-  // Persistent, one segment per lane at a time: every iteration takes one
-  // hit step of each lane's segment, and a lane whose segment is done writes
-  // its outputs and takes the next one from its wave's pool (64 consecutive
-  // segments claimed with one atomic), so lanes do not wait for the longest
-  // segment of their wave.  Each segment sees the same operation sequence.
-  int g = -1, u = 0, k = 0, nh = 0, r_first = 0, r_last = 0;
-  int64_t h0 = 0;
-  bool ok = false;
-  float zin = 0.0f;
-  KState st;
-  CmpFit fit;
-  float4 nxt = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-  int pnext = 0, pend = 0;
-  bool exhausted = false;
-  for (;;) {
-    if (g >= 0 && k >= nh) {
-      // the segment is done: its outer end and pairing words
-      P2Out o;
-      o.x = st.x;
-#pragma unroll
-      for (int j = 0; j < 5; ++j) o.p[j] = st.p[j];
-#pragma unroll
-      for (int j = 0; j < 15; ++j) o.C[j] = st.C[j];
-      o.ok = ok ? 1 : 0;
-      Q.seg_out[g] = o;
-      Q.seg_unit[g] = u;
-      Q.seg_nh[g] = nh;
-      Q.seg_hb[g] = h0;
-      Q.seg_rows[g] = make_int2(r_first, r_last);
-      Q.seg_zin[g] = zin;
-      Q.seg_zout[g] = st.p[1] + zin;
-      Q.best_a[g] = ~0ull;
-      Q.best_b[g] = ~0ull;
-      Q.next[g] = -1;
-      Q.prev[g] = -1;
-      g = -1;
+  const P2Quant quant(q);
+  for (int i0 = blockIdx.x * 64; i0 < n; i0 += gridDim.x * 64) {
+    const bool mine = i0 + lane < n;
+    const int g = Q.order[mine ? i0 + lane : i0];  // spare lanes go along with the first one's
+    const int u = p2_unit_of(Q, g);
+    const tpcca_track_t &t = p2_track(B, Q, g, u);
+    const int64_t h0 = p2_hit0(B, t, u);
+    const int nh = t.n_hits;
+    const float zin = t.p[1];
+    KState st = p2_inner(t);
+    const float4 *hr = Q.hrec + h0;
+    const float4 c0 = hr[0];
+    float4 nxt = hr[nh > 1 ? 1 : 0];
+    const int r_first = __float_as_int(c0.z);
+    int r_last = r_first;
+    bool ok = kf_propagate(P, st, s_rx[r_first]);
+    // Sec. 3 compression of the segment in the same pass over its hits
+    // (the two fits are independent chains of operations)
+    const int32_t yq0 = quant.y(c0.x), zq0 = quant.z(c0.y);
+    if (mine) {
+      int32_t *rc = Q.rec + 6 * (int64_t)g;
+      rc[0] = r_first;
+      rc[1] = yq0;
+      rc[2] = zq0;
+      rc[3] = (int32_t)__float_as_uint(t.p[2]);
+      rc[4] = (int32_t)__float_as_uint(t.p[3]);
+      rc[5] = (int32_t)__float_as_uint(t.p[4]);
     }
-    const unsigned long long idle = __ballot(g < 0);
-    if (idle) {
-      if (pnext == pend && !exhausted) {
-        int base = 0;
-        if (lane == 0) base = atomicAdd(&Q.cnt->seg_next, 64);
-        base = __shfl(base, 0, 64);
-        if (base >= n) {
-          exhausted = true;
-        } else {
-          pnext = base;
-          pend = min(base + 64, n);
-        }
+    CmpFit fit;
+    fit.start(P, q, s_rx, r_first, yq0, zq0, t.p[2], t.p[3], t.p[4]);
+    // residuals: one aligned 16-B record per hit (row step, y, z, 0)
+    s_h0[lane] = h0;
+    s_nh[lane] = mine ? nh : 0;
+    s_res[lane][0] = make_int4(0, 0, 0, 0);
+    for (int k = 1;; ++k) {
+      const bool more = __any(k < nh);
+      if ((k & (kP2Out - 1)) == 0 || !more) {
+        const int first = (k - 1) & ~(kP2Out - 1), e = lane & (kP2Out - 1);
+        wave_lds_order();
+#pragma unroll
+        for (int src = lane / kP2Out; src < 64; src += 64 / kP2Out)
+          if (first + e < min(k, s_nh[src]))
+            reinterpret_cast<int4 *>(Q.res)[s_h0[src] + first + e] = s_res[src][e];
+        wave_lds_order();
       }
-      if (pnext < pend) {
-        const int take = min(__popcll(idle), pend - pnext);
-        const int rank = __popcll(idle & below);
-        if (g < 0 && rank < take) {
-          g = Q.order[pnext + rank];
-          u = p2_unit_of(Q, g);
-          const tpcca_track_t &t = p2_track(B, Q, g, u);
-          h0 = p2_hit0(B, t, u);
-          nh = t.n_hits;
-          zin = t.p[1];
-          st = p2_inner(t);
-          const float4 *hr = Q.hrec + h0;
-          const float4 c0 = hr[0];
-          r_first = __float_as_int(c0.z);
-          r_last = r_first;
-          ok = kf_propagate(P, st, s_rx[r_first]);
-          // Sec. 3 compression of the segment in the same pass over its hits
-          // (the two fits are independent chains of operations)
-          const int32_t yq0 = p2_quant(c0.x, q.qy), zq0 = p2_quant(c0.y, q.qz);
-          int32_t *rc = Q.rec + 6 * (int64_t)g;
-          rc[0] = r_first;
-          rc[1] = yq0;
-          rc[2] = zq0;
-          rc[3] = (int32_t)__float_as_uint(t.p[2]);
-          rc[4] = (int32_t)__float_as_uint(t.p[3]);
-          rc[5] = (int32_t)__float_as_uint(t.p[4]);
-          fit.start(P, q, s_rx, r_first, yq0, zq0, t.p[2], t.p[3], t.p[4]);
-          // residuals: one aligned 16-B record per hit (row step, y, z, 0)
-          reinterpret_cast<int4 *>(Q.res)[h0] = make_int4(0, 0, 0, 0);
-          nxt = nh > 1 ? hr[1] : c0;
-          k = 1;
-        }
-        pnext += take;
+      if (!more) break;
+      if (k < nh) {
+        const float4 c = nxt;
+        nxt = hr[min(k + 1, nh - 1)];  // the next record's load overlaps this step
+        const int r = __float_as_int(c.z);
+        if (ok && !kf_propagate(P, st, s_rx[r])) ok = false;
+        int32_t py, pz;
+        const bool pok = fit.predict(P, quant, s_rx, r, py, pz);
+        const int32_t yq = quant.y(c.x), zq = quant.z(c.y);
+        s_res[lane][k & (kP2Out - 1)] = make_int4(r - r_last, yq - py, zq - pz, 0);
+        fit.take(P, q, pok, yq, zq);
+        r_last = r;
       }
     }
-    if (!__any(g >= 0)) break;
-    if (g >= 0 && k < nh) {
-      const float4 c = nxt;
-      if (k + 1 < nh) nxt = Q.hrec[h0 + k + 1];  // the next record's load overlaps this step
-      const int r = __float_as_int(c.z);
-      if (ok && !kf_propagate(P, st, s_rx[r])) ok = false;
-      int32_t py, pz;
-      const bool pok = fit.predict(P, q, s_rx, r, py, pz);
-      const int32_t yq = p2_quant(c.x, q.qy), zq = p2_quant(c.y, q.qz);
-      reinterpret_cast<int4 *>(Q.res)[h0 + k] = make_int4(r - r_last, yq - py, zq - pz, 0);
-      fit.take(P, q, pok, yq, zq);
-      r_last = r;
-      ++k;
-    }
+    if (!mine) continue;
+    // its outer end and pairing words
+    P2Out o;
+    o.x = st.x;
+#pragma unroll
+    for (int j = 0; j < 5; ++j) o.p[j] = st.p[j];
+#pragma unroll
+    for (int j = 0; j < 15; ++j) o.C[j] = st.C[j];
+    o.ok = ok ? 1 : 0;
+    Q.seg_out[g] = o;
+    Q.seg_unit[g] = u;
+    Q.seg_nh[g] = nh;
+    Q.seg_hb[g] = h0;
+    Q.seg_rows[g] = make_int2(r_first, r_last);
+    Q.seg_zin[g] = zin;
+    Q.seg_zout[g] = st.p[1] + zin;
+    Q.best_a[g] = ~0ull;
+    Q.best_b[g] = ~0ull;
+    Q.next[g] = -1;
+    Q.prev[g] = -1;
   }
 }
 
@@ -742,9 +751,12 @@ __global__ __launch_bounds__(256) void k_p2_final_hits(Bufs B, P2Bufs Q) {
 // Persistent, one final track per lane at a time: every iteration takes one
 // step (a hit, a rotation into the next segment's frame, or a step to the
 // axis) of each lane's track, and a lane whose track is done takes the next
-// one from its wave's pool (64 consecutive tracks claimed with one atomic),
-// so tracks of 1 and of 18 segments do not hold each other up.  Each track
-// sees the same operation sequence.
+// one from its wave's pool (64 consecutive tracks, the first by the wave's
+// number and the next ones claimed with one atomic), so tracks of 1 and of 18
+// segments do not hold each other up.  Each track sees the same operation
+// sequence.  Blocks are single waves, spread over the chip as in the segment
+// preparation: central event 342 -> 201 us, frame of 16 M clusters 712 -> 315
+// (the pools of blocks of 256 filled a third of the CUs).
 __device__ __forceinline__ void p2_final_failed(const P2Bufs &Q, int f) {
   tpcca_final_t &o = Q.finals[f];
   o.status = 2;
@@ -763,7 +775,7 @@ __device__ __forceinline__ void p2_final_failed(const P2Bufs &Q, int f) {
   o.z_conv = 0.0f;
 }
 
-__global__ __launch_bounds__(256) void k_p2_refit(Bufs B, P2Bufs Q, ParamsDev P, P2Params q) {
+__global__ __launch_bounds__(64) void k_p2_refit(Bufs B, P2Bufs Q, ParamsDev P, P2Params q) {
   // the pad-row positions in LDS: a row step reads its plane without a
   // global load on the dependent chain
   __shared__ float s_rx[kMaxRows + 1];
@@ -780,8 +792,9 @@ __global__ __launch_bounds__(256) void k_p2_refit(Bufs B, P2Bufs Q, ParamsDev P,
   float zr = 0.0f, chi2 = 0.0f, x0 = 0.0f;
   KState st;
   float4 nxt = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-  int pnext = 0, pend = 0;
-  bool exhausted = false;
+  // the first 64 of the wave go without the counter
+  int pnext = min(n, (int)blockIdx.x * 64), pend = min(n, pnext + 64);
+  bool exhausted = (int)gridDim.x * 64 >= n;
   for (;;) {
     // ---- transitions of lanes whose current segment, hits or axis steps
     // are done
@@ -834,7 +847,7 @@ __global__ __launch_bounds__(256) void k_p2_refit(Bufs B, P2Bufs Q, ParamsDev P,
       if (pnext == pend && !exhausted) {
         int base = 0;
         if (lane == 0) base = atomicAdd(&Q.cnt->fin_next, 64);
-        base = __shfl(base, 0, 64);
+        base = __shfl(base, 0, 64) + (int)gridDim.x * 64;
         if (base >= n) {
           exhausted = true;
         } else {
@@ -1091,33 +1104,115 @@ __global__ __launch_bounds__(256) void k_p2_flags(Bufs B, P2Bufs Q, P2Params q, 
   }
 }
 
-__global__ __launch_bounds__(256) void k_p2_decompress(ParamsDev P, P2Params q, const float *row_x, int n_seg,
-                                                      int R, const int32_t *n_hits, const int64_t *hit_begin,
-                                                      const int32_t *rec, const int32_t *res, int32_t *yq,
-                                                      int32_t *zq, uint8_t *rows) {
-  for (int g = blockIdx.x * blockDim.x + threadIdx.x; g < n_seg; g += gridDim.x * blockDim.x) {
-    const int32_t *rc = rec + 6 * (int64_t)g;
-    const int64_t h0 = hit_begin[g];
-    int r = rc[0];
-    if (r < 0 || r >= R) continue;
-    CmpFit fit;
-    fit.start(P, q, row_x, r, rc[1], rc[2], __uint_as_float((uint32_t)rc[3]), __uint_as_float((uint32_t)rc[4]),
-              __uint_as_float((uint32_t)rc[5]));
-    yq[h0] = rc[1];
-    zq[h0] = rc[2];
-    rows[h0] = (uint8_t)r;
-    for (int j = 1; j < n_hits[g]; ++j) {
-      const int4 rs = reinterpret_cast<const int4 *>(res)[h0 + j];
-      r += rs.x;
-      if (r < 0 || r >= R) break;  // corrupt input: leave the rest untouched
-      int32_t py, pz;
-      const bool ok = fit.predict(P, q, row_x, r, py, pz);
-      const int32_t y = rs.y + py, z = rs.z + pz;
-      yq[h0 + j] = y;
-      zq[h0 + j] = z;
-      rows[h0 + j] = (uint8_t)r;
-      fit.take(P, q, ok, y, z);
+// Decompression, a lane per segment: its hits are a serial chain (predict, add
+// the residual, update).  Each wave has a set of `per` neighbouring segments,
+// takes them by length (a counting sort in LDS) and gives a lane the next one
+// when its own is done, so that lanes do not wait for the longest of 64
+// segments: a frame's have 1 to 159 hits, 51 on average.  Bound by instruction
+// issue; 149 thousand segments 614 -> 226 us against a thread each in input
+// order.
+constexpr int kDecSet = 1024, kDecBins = 256;
+__global__ __launch_bounds__(64) void k_p2_decompress(ParamsDev P, P2Params q, const float *row_x, int n_seg, int R,
+                                                     int per, const int32_t *n_hits, const int64_t *hit_begin,
+                                                     const int32_t *rec, const int32_t *res, int32_t *yq,
+                                                     int32_t *zq, uint8_t *rows) {
+  __shared__ float s_rx[kMaxRows + 1];
+  __shared__ int hist[kDecBins];
+  __shared__ uint16_t list[kDecSet];
+  // hits under way (y, z, position with the row in its top byte): eight of each
+  // lane go out together, a lane's by eight lanes (hit by hit the stores took 120
+  // of 351 us on a frame of 7.6 M hits)
+  __shared__ int4 s_out[64][kP2Out + 1];
+  const int lane = threadIdx.x;
+  for (int i = lane; i < R; i += 64) s_rx[i] = row_x[i];
+  const P2Quant quant(q);
+  for (int64_t s0 = (int64_t)blockIdx.x * per; s0 < n_seg; s0 += (int64_t)gridDim.x * per) {
+    const int m = (int)min((int64_t)per, n_seg - s0);
+    // the set by descending length
+    for (int i = lane; i < kDecBins; i += 64) hist[i] = 0;
+    __syncthreads();
+    auto bin = [&](int i) { return kDecBins - 1 - min(max(n_hits[s0 + i], 0), kDecBins - 1); };
+    for (int i = lane; i < m; i += 64) atomicAdd(&hist[bin(i)], 1);
+    __syncthreads();
+    int carry = 0;
+    for (int i = lane; i < kDecBins; i += 64) {
+      const int v = hist[i], incl = wave_scan_dpp(v);
+      hist[i] = carry + incl - v;
+      carry += __builtin_amdgcn_readlane(incl, 63);
     }
+    __syncthreads();
+    for (int i = lane; i < m; i += 64) list[atomicAdd(&hist[bin(i)], 1)] = (uint16_t)i;
+    __syncthreads();
+    int next = 0, j = 0, nh = 0, r = 0;  // a lane is busy while j < nh
+    int held = 0;                        // the lane's hits under way
+    auto put = [&](int64_t h, int32_t y, int32_t z) {
+      const unsigned long long w = ((unsigned long long)r << 56) | (unsigned long long)h;
+      s_out[lane][held++] = make_int4(y, z, (int)(unsigned int)w, (int)(unsigned int)(w >> 32));
+    };
+    int64_t h0 = 0;
+    int4 rs = make_int4(0, 0, 0, 0);
+    CmpFit fit;
+    for (;;) {
+      const unsigned long long idle = __ballot(j >= nh);
+      if (idle && next < m) {
+        const int at = next + __popcll(idle & ((1ull << lane) - 1));
+        if (j >= nh && at < m) {
+          const int64_t g = s0 + list[at];
+          const int32_t *rc = rec + 6 * g;
+          h0 = hit_begin[g];
+          r = rc[0];
+          j = nh = 0;
+          if (r >= 0 && r < R) {
+            nh = n_hits[g];
+            j = 1;
+            if (nh > 1) rs = reinterpret_cast<const int4 *>(res)[h0 + 1];
+            fit.start(P, q, s_rx, r, rc[1], rc[2], __int_as_float(rc[3]), __int_as_float(rc[4]),
+                      __int_as_float(rc[5]));
+            put(h0, rc[1], rc[2]);
+          }
+        }
+        next = min(m, next + __popcll(idle));
+      }
+      const bool more = __any(j < nh);
+      if (__any(held >= kP2Out - 1) || (!more && next >= m)) {  // a step adds up to two
+        wave_lds_order();
+        const int e = lane & (kP2Out - 1);
+#pragma unroll
+        for (int s = 0; s < 64; s += 64 / kP2Out) {
+          const int src = s + lane / kP2Out;
+          const int have = __shfl(held, src, 64);
+          if (e < have) {
+            const int4 v = s_out[src][e];
+            const int64_t h = ((int64_t)(v.w & 0xFFFFFF) << 32) | (unsigned int)v.z;
+            yq[h] = v.x;
+            zq[h] = v.y;
+            rows[h] = (uint8_t)((unsigned int)v.w >> 24);
+          }
+        }
+        held = 0;
+        wave_lds_order();
+      }
+      if (!more) {
+        if (next >= m) break;
+        continue;
+      }
+      if (j < nh) {
+        const int4 c = rs;
+        rs = reinterpret_cast<const int4 *>(res)[h0 + min(j + 1, nh - 1)];  // overlaps this step
+        r += c.x;
+        if (r < 0 || r >= R) {
+          nh = 0;  // corrupt input: leave the rest untouched
+        } else {
+          int32_t py, pz;
+          const bool ok = fit.predict(P, quant, s_rx, r, py, pz);
+          const int32_t y = c.y + py, z = c.z + pz;
+          put(h0 + j, y, z);
+          fit.take(P, q, ok, y, z);
+          ++j;
+        }
+      }
+    }
+    __syncthreads();
   }
 }
 
@@ -1233,7 +1328,7 @@ hipError_t p2_launch_merge(const Bufs &B, const P2Bufs &Q, const ParamsDev &P, c
   k_p2_seg_index<<<1, 1024, 0, s>>>(B, Q, R);
   k_p2_hits<<<p2_grid(hit_span, 256, 16384), 256, 0, s>>>(B, Q, R);
   p2_len_order(B, Q, SegLen{}, seg_cap, s);
-  k_p2_seg_prep<<<p2_grid(seg_cap, 256, 2048), 256, 0, s>>>(B, Q, P, q);  // persistent
+  k_p2_seg_prep<<<p2_grid(seg_cap, 64, 4096), 64, 0, s>>>(B, Q, P, q);
   k_p2_zrange<<<std::min(n_units, 4096), 256, 0, s>>>(Q);
   k_p2_bin_count<<<gs, 256, 0, s>>>(Q);
   k_p2_bin_scan<<<std::min(n_units, 4096), 1024, 0, s>>>(Q, R);
@@ -1264,7 +1359,7 @@ hipError_t p2_launch_pairs(const Bufs &B, const P2Bufs &Q, const ParamsDev &P, c
   if (e != hipSuccess) return e;
   k_p2_final_hits<<<p2_grid((int64_t)seg_cap * 16, 256, 16384), 256, 0, s>>>(B, Q);
   p2_len_order(B, Q, FinLen{}, seg_cap, s);
-  k_p2_refit<<<p2_grid(seg_cap, 256, 2048), 256, 0, s>>>(B, Q, P, q);  // persistent
+  k_p2_refit<<<p2_grid(seg_cap, 64, 4096), 64, 0, s>>>(B, Q, P, q);  // persistent
   // vertex candidates, compacted with their sort keys
   e = p2_scan(GetCand{Q.finals, q}, PutCand{Q.finals, Q.vkey[0], Q.vval[0]}, &Q.cnt->n_final, seg_cap,
               Q.scan_tmp, &Q.cnt->n_cand, nullptr, s);
@@ -1328,8 +1423,13 @@ hipError_t p2_launch_decompress(const ParamsDev &P, const P2Params &q, const flo
                                 const int32_t *n_hits, const int64_t *hit_begin, const int32_t *rec,
                                 const int32_t *res, int32_t *yq, int32_t *zq, uint8_t *rows, hipStream_t s) {
   if (n_seg <= 0) return hipSuccess;
-  k_p2_decompress<<<p2_grid(n_seg, 256, 8192), 256, 0, s>>>(P, q, row_x, n_seg, P.n_rows, n_hits, hit_begin, rec,
-                                                           res, yq, zq, rows);
+  // up to 64 segments a wave while a wave per SIMD holds them all (a lone wave
+  // steps twice as fast as one of three); then a wave per SIMD until each has
+  // 256, where the longest segment no longer sets the time, and at most four
+  constexpr int kSimds = 1024;
+  const int waves = n_seg <= 64 * kSimds ? (n_seg + 63) / 64 : kSimds * std::min(4, std::max(1, n_seg / (256 * kSimds)));
+  const int per = std::min(kDecSet, (n_seg + waves - 1) / waves);
+  k_p2_decompress<<<waves, 64, 0, s>>>(P, q, row_x, n_seg, P.n_rows, per, n_hits, hit_begin, rec, res, yq, zq, rows);
   return hipGetLastError();
 }
 

@@ -207,3 +207,77 @@ def test_chains_around_the_lds_unit_sizes(tpcca, torch_cuda, row_x, n):
             for s, (c, r) in enumerate(parts):
                 _parity.compare_unit_stagewise(ctx, 0, s, c, r, refs[s])
 
+
+
+@pytest.fixture(scope="module")
+def stored(tpcca, row_x):
+    """Compressed segments of a sector, cut to lengths from 0 hits on, and what the
+    oracle reads back of them."""
+    b = tpcgen.one_sector(seed=12)
+    cl, row, slot, sec, _ = b.unit(0)
+    with tpcca.Context(row_x) as ctx:
+        ctx.load_sector(slot, sec, cl, row)
+        ctx.run_all()
+        nh = ctx.get_tracks(slot, sec)[0]["n_hits"].astype(np.int32)
+        ctx.phase2()
+        rec, res = ctx.get_compressed(slot, sec)
+    begin = np.cumsum(nh) - nh
+    return rec, [res[o:o + k] for o, k in zip(begin, nh)], oracle.decompress(row_x, nh, rec, res)
+
+
+# the sets of a wave: 64 segments and fewer, then up to a wave per SIMD, to four, and beyond a set's room
+@pytest.mark.parametrize("n_seg", [1, 63, 65, 65536, 65537, 524288, 4194304 + 7])
+def test_decompression_of_any_number_of_segments(tpcca, torch_cuda, row_x, stored, n_seg):
+    """Segments of 0 to 159 hits in any order, with gaps between their hits; one
+    of them turns to a row that is not there and ends before it."""
+    torch = torch_cuda
+    rec, res, (y, z, r) = stored
+    first = np.cumsum([0] + [len(x) for x in res])
+    rng = np.random.default_rng(n_seg)
+    cut = [(u, k) for u in range(len(res)) for k in ((0, 1, 2, len(res[u])) if n_seg < 100000 else (0, 1, 2, 9))]
+    pick = rng.integers(0, len(cut), n_seg)
+    unit, n = np.array(cut, np.int32).T[:, pick]
+    begin = np.cumsum(np.maximum(n, 1) + rng.integers(0, 2, n_seg)) - np.maximum(n, 1)  # the first is written of 0, too
+    total = int(begin[-1] + max(1, n[-1]) + 1)
+    at = np.repeat(begin - (np.cumsum(np.maximum(n, 1)) - np.maximum(n, 1)), np.maximum(n, 1)) + np.arange(
+        np.maximum(n, 1).sum())
+    src = np.repeat(first[unit] - (np.cumsum(np.maximum(n, 1)) - np.maximum(n, 1)), np.maximum(n, 1)) + np.arange(
+        np.maximum(n, 1).sum())
+    all_res = np.zeros((total, 4), np.int32)
+    all_res[at, :3] = np.concatenate(res)[src]
+    want = [np.full(total, -5, np.int32), np.full(total, -6, np.int32), np.full(total, 255, np.uint8)]
+    for w, v in zip(want, (y, z, r)):
+        w[at] = v[src]
+    bad = int(np.argmax(n))
+    if n[bad] > 2:
+        all_res[begin[bad] + 2, 0] = 1000
+        for w, v in zip(want, (-5, -6, 255)):
+            w[begin[bad] + 2:begin[bad] + n[bad]] = v
+    print(f"{n_seg} segments, {len(at)} hits", flush=True)
+    d = [torch.from_numpy(np.ascontiguousarray(a)).cuda() for a in (n, begin.astype(np.int64), rec[unit], all_res)]
+    out = [torch.full((total,), v, dtype=t, device="cuda")
+           for v, t in ((-5, torch.int32), (-6, torch.int32), (255, torch.uint8))]
+    torch.cuda.synchronize()
+    with tpcca.Context(row_x) as ctx:
+        ctx.decompress(n_seg, *d, *out)
+        ctx.sync()
+    for o, w in zip(out, want):
+        assert np.array_equal(o.cpu().numpy(), w)
+
+
+@pytest.mark.parametrize("qy, qz", [(0.01, 0.01), (0.037, 2.0 ** -60), (2.0 ** 60, 0.3), (1e-20, 0.01), (0.01, 1e22)])
+def test_compression_steps_inside_and_outside_the_shared_reciprocals(tpcca, row_x, qy, qz):
+    """Quantisation steps where the quotients share a reciprocal and where they are
+    divisions; segments of every length, the last wave partly filled."""
+    b = tpcgen.one_sector(seed=13)
+    cl, row, slot, sec, _ = b.unit(0)
+    seg, hb, hits = oracle.segments_of([oracle.run_sector(cl, row, row_x)])
+    rec, res = oracle.compress(cl, row, row_x, seg, hb, hits, p2=oracle.default_p2params(cmp_qy=qy, cmp_qz=qz))
+    assert seg.shape[0] % 64
+    with tpcca.Context(row_x) as ctx:
+        ctx.load_sector(slot, sec, cl, row)
+        ctx.run_all()
+        ctx.set_phase2_params(cmp_qy=qy, cmp_qz=qz)
+        ctx.phase2()
+        grec, gres = ctx.get_compressed(slot, sec)
+    assert np.array_equal(grec, rec) and np.array_equal(gres, res)
