@@ -34,8 +34,11 @@ inline int row_class(int64_t units, int64_t hits, int R) {
 // Units of up to kLdsUnit hits (133 of a CU's 160 KB) have their chains built in
 // LDS, one block per unit (kLdsUnitSmall: several blocks share a CU).  The second
 // kernel sums the tracklet counts of all units before its own, which bounds the
-// units.
+// units.  From kManyUnits on (a block for every CU) the units up to kLdsUnitSmall
+// have a launch of their own, as one of the larger blocks fills a CU, and the
+// assignment is written per unit as well.
 constexpr int kLdsUnitSmall = 8192, kLdsUnit = 40960, kLdsUnits = 4096;
+constexpr int kManyUnits = 256;
 inline int unit_class(int64_t units, int64_t largest) {
   return units > kLdsUnits ? 0 : largest <= kLdsUnitSmall ? kLdsUnitSmall : largest <= kLdsUnit ? kLdsUnit : 0;
 }

@@ -995,7 +995,7 @@ __global__ __launch_bounds__(kBlock) void k_chain(Bufs B, ParamsDev P, int run) 
 // ten launches with scans between them for the same.  Bound by a serial chain
 // (159 LDS reads, 15 us of a peripheral event); before and after, both kernels
 // against the ten: peripheral event 71 -> 24 us, central event 109 -> 45, 64
-// minimum-bias events 480 -> 185.
+// minimum-bias events 480 -> 153.
 template <int kCap>
 struct ChainUnit {
   uint16_t up[kCap];
@@ -1011,13 +1011,14 @@ __device__ __forceinline__ uint32_t *unit_maps(const Bufs &B, const UnitDev &U) 
 }
 
 template <int kCap, int kT>
-__global__ __launch_bounds__(kT) void k_chain_units(Bufs B, ParamsDev P, int run, int R) {
+__global__ __launch_bounds__(kT) void k_chain_units(Bufs B, ParamsDev P, int run, int R, int above) {
   __shared__ ChainUnit<kCap> S;
   const RunDev &rd = B.runs[run];
   const int lane = threadIdx.x & 63;
   for (int w = blockIdx.x; w < rd.u1 - rd.u0; w += gridDim.x) {
     const UnitDev U = B.units[rd.u0 + w];
-    const int n = min(U.n, kCap), words = (n + 31) >> 5;
+    if (U.n <= above || U.n > kCap) continue;  // another launch's
+    const int n = U.n, words = (n + 31) >> 5;
     const int32_t *upc = B.upc + U.cl_begin, *dnc = B.dnc + U.cl_begin;
     if (threadIdx.x == 0) S.starts = S.tracklets = 0;
     for (int i = threadIdx.x; i < words; i += kT) S.by_hit[i] = S.by_id[i] = 0u;
@@ -1424,6 +1425,12 @@ __global__ __launch_bounds__(kBlock) void k_claim(Bufs B, ParamsDev P, int run) 
 // reads.
 constexpr int kGrp = 8;
 constexpr int kWonGrp = 8;
+// Group widths of slots read at once, so that a wave waits for the slots and for
+// what they point to once in two or four widths: central event, output pass 31 ->
+// 28 us, acceptance pass 25 -> 14; 64 minimum-bias events 426 -> 402 and 163 ->
+// 135 (four in the acceptance pass read too much of the tracklets that lose: a
+// frame of 33 M clusters 541 us, 497 with two).
+constexpr int kAhead = 4, kWonAhead = 2;
 
 // Count the hits a tracklet won, record which, accept or reject (a tracklet
 // that has already lost too many hits is rejected without reading the rest).
@@ -1447,20 +1454,31 @@ __global__ __launch_bounds__(kBlock) void k_won(Bufs B, ParamsDev P, int run) {
       const int n = o.n_hits;
       unsigned long long cur = 0;
       int won = 0;
-      for (int j0 = 0; j0 < n; j0 += kG) {
-        const int j = j0 + gl;
-        const bool w = j < n && B.owner[slot_hit(hl[j], ucl)] == key;
-        const unsigned int bits = (unsigned int)(__ballot(w) >> g0) & ((1u << kG) - 1);
+      // kWonAhead groups of slots in flight: the slots, then their owner words
+      for (int j0 = 0; j0 < n; j0 += kG * kWonAhead) {
+        int h[kWonAhead];
+        bool w[kWonAhead];
+#pragma unroll
+        for (int q = 0; q < kWonAhead; ++q) h[q] = hl[min(j0 + q * kG + gl, n - 1)];
+#pragma unroll
+        for (int q = 0; q < kWonAhead; ++q) w[q] = B.owner[slot_hit(h[q], ucl)] == key;
+        unsigned int bits = 0;
+#pragma unroll
+        for (int q = 0; q < kWonAhead; ++q) {
+          const bool won_q = w[q] && j0 + q * kG + gl < n;
+          bits |= ((unsigned int)(__ballot(won_q) >> g0) & ((1u << kG) - 1)) << (q * kG);
+        }
         won += __popc(bits);
         cur |= (unsigned long long)bits << (j0 & 63);
-        if (((j0 + kG) & 63) == 0 || j0 + kG >= n) {  // a 64-slot word is complete
+        const int done = j0 + kG * kWonAhead;
+        if ((done & 63) == 0 || done >= n) {  // a 64-slot word is complete
           if (gl == 0) wm[j0 >> 6] = cur;
           cur = 0;
         }
         // stop once even winning every remaining hit could not reach the
         // acceptance bounds (the won mask is read for accepted tracks only)
-        const int most = won + (n - (j0 + kG));
-        if (j0 + kG < n && (most < P.min_hits || most * 100 < P.own_pct * n)) break;
+        const int most = won + (n - done);
+        if (done < n && (most < P.min_hits || most * 100 < P.own_pct * n)) break;
       }
       if (won >= P.min_hits && won * 100 >= P.own_pct * n)
         v = (1ull << 40) | (unsigned long long)won;
@@ -1608,7 +1626,8 @@ __global__ __launch_bounds__(1024) void k_accept_small(Bufs B, int run) {
 // Compaction of accepted tracks, a group of kGrp lanes per tracklet:
 // parameters, won hits in ascending rows (inward hits were stored after the
 // pass-1 hits, in descending rows) and the per-cluster assignment
-// (unit-local track index).
+// (unit-local track index; kAssign false: by k_assign_units).
+template <bool kAssign>
 __global__ __launch_bounds__(kBlock) void k_output(Bufs B, ParamsDev P, int run) {
   const RunDev &rd = B.runs[run];
   const int R = P.n_rows;
@@ -1638,33 +1657,80 @@ __global__ __launch_bounds__(kBlock) void k_output(Bufs B, ParamsDev P, int run)
     const unsigned long long m2 = nh > 128 ? wmp[2] : 0ull;
     const unsigned long long m3 = nh > 192 ? wmp[3] : 0ull;
     int w = 0;
-    for (int j0 = 0; j0 < nh; j0 += kGrp) {
-      const int j = j0 + gl;
-      // slot of the j-th hit in row order
-      const int slot = j < ne ? n1 + ne - 1 - j : j - ne;
-      const unsigned long long m = slot < 64 ? m0 : slot < 128 ? m1 : slot < 192 ? m2 : m3;
-      const bool won = j < nh && ((m >> (slot & 63)) & 1ull);
-      const unsigned int bits = (unsigned int)(__ballot(won) >> g0) & ((1u << kGrp) - 1);
-      if (won) {
-        const int id = B.sid[slot_hit(hl[slot], ucl)];
-        B.hits_out[h0 + w + __popc(bits & ((1u << gl) - 1))] = id;
-        B.assign[ucl + id] = local_track;
+    for (int j0 = 0; j0 < nh; j0 += kGrp * kAhead) {
+      int id[kAhead];
+      bool won[kAhead];
+#pragma unroll
+      for (int q = 0; q < kAhead; ++q) {
+        const int j = min(j0 + q * kGrp + gl, nh - 1);
+        // slot of the j-th hit in row order
+        const int slot = j < ne ? n1 + ne - 1 - j : j - ne;
+        const unsigned long long m = slot < 64 ? m0 : slot < 128 ? m1 : slot < 192 ? m2 : m3;
+        won[q] = j0 + q * kGrp + gl < nh && ((m >> (slot & 63)) & 1ull);
+        id[q] = hl[slot];
       }
-      w += __popc(bits);
+#pragma unroll
+      for (int q = 0; q < kAhead; ++q) id[q] = B.sid[slot_hit(id[q], ucl)];
+#pragma unroll
+      for (int q = 0; q < kAhead; ++q) {
+        const unsigned int bits = (unsigned int)(__ballot(won[q]) >> g0) & ((1u << kGrp) - 1);
+        if (won[q]) {
+          B.hits_out[h0 + w + __popc(bits & ((1u << gl) - 1))] = id[q];
+          if (kAssign) B.assign[ucl + id[q]] = local_track;
+        }
+        w += __popc(bits);
+      }
     }
-    if (gl == 0) {
-      tpcca_track_t tr;
-      tr.x_ref = o.x_ref;
-      for (int q = 0; q < 5; ++q) tr.p[q] = o.p[q];
-      for (int q = 0; q < 15; ++q) tr.cov[q] = o.cov[q];
-      tr.chi2 = o.chi2;
-      tr.ndf = o.ndf;
-      tr.n_hits = w;
-      tr.hit_offset = (int32_t)(h0 - hb);
-      tr.sector = B.units[u].sector;
-      tr.start_id = o.start_id;
-      B.tracks[k] = tr;
+    // the record, a word per lane: reference plane, parameters and covariance
+    // (words 0 to 20) as in the tracklet's, then the rest
+    static_assert(sizeof(tpcca_track_t) == 27 * 4 && offsetof(tpcca_tracklet_t, x_ref) == 8 * 4 &&
+                  offsetof(tpcca_tracklet_t, p) == 11 * 4 && offsetof(tpcca_tracklet_t, cov) == 16 * 4 &&
+                  offsetof(tpcca_track_t, p) == 1 * 4 && offsetof(tpcca_track_t, cov) == 6 * 4 &&
+                  offsetof(tpcca_track_t, chi2) == 21 * 4 && offsetof(tpcca_track_t, ndf) == 22 * 4 &&
+                  offsetof(tpcca_track_t, n_hits) == 23 * 4 && offsetof(tpcca_track_t, hit_offset) == 24 * 4 &&
+                  offsetof(tpcca_track_t, sector) == 25 * 4 && offsetof(tpcca_track_t, start_id) == 26 * 4 &&
+                  offsetof(tpcca_tracklet_t, chi2) == 9 * 4 && offsetof(tpcca_tracklet_t, ndf) == 5 * 4 &&
+                  offsetof(tpcca_tracklet_t, start_id) == 0, "record words");
+    const int32_t *from = reinterpret_cast<const int32_t *>(&o);
+    int32_t *to = reinterpret_cast<int32_t *>(B.tracks + k);
+    const int sector = B.units[u].sector;
+#pragma unroll
+    for (int d0 = 0; d0 < 27; d0 += kGrp) {
+      const int d = d0 + gl;
+      const int at = d == 0 ? 8 : d <= 20 ? d + 10 : d == 21 ? 9 : d == 22 ? 5 : 0;
+      int32_t v = from[at];
+      v = d == 23 ? w : d == 24 ? (int32_t)(h0 - hb) : d == 25 ? sector : v;
+      if (d < 27) to[d] = v;
     }
+  }
+}
+
+// The assignment of units that fit a CU's LDS, for runs with units for every
+// CU: a block per unit collects it there from the tracks' hits and writes it in
+// one piece.  Cluster by cluster the output pass's stores go to 64 places each
+// (64 minimum-bias events: 227 of its 402 us, against 67 us here); with fewer
+// units than CUs the extra launch costs what it gains.
+template <int kCap, int kT>
+__global__ __launch_bounds__(kT) void k_assign_units(Bufs B, int run, int above) {
+  __shared__ int16_t s_track[kCap];
+  const RunDev &rd = B.runs[run];
+  for (int u = rd.u0 + (int)blockIdx.x; u < rd.u1; u += gridDim.x) {
+    const UnitDev U = B.units[u];
+    if (U.n <= above || U.n > kCap) continue;  // another launch's
+    const tpcca_unit_result_t r = B.unit_res[u];
+    const int n = U.n;
+    for (int i = threadIdx.x; i < n; i += kT) s_track[i] = -1;
+    __syncthreads();
+    const int gl = threadIdx.x & 15;  // sixteen lanes per track
+    for (int k = (int)threadIdx.x >> 4; k < r.n_tracks; k += kT >> 4) {
+      const tpcca_track_t &t = B.tracks[r.track_begin + k];
+      const int32_t *hits = B.hits_out + r.hit_begin + t.hit_offset;
+      const int nh = t.n_hits;
+      for (int j = gl; j < nh; j += 16) s_track[hits[j]] = (int16_t)k;
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < n; i += kT) B.assign[U.cl_begin + i] = s_track[i];
+    __syncthreads();
   }
 }
 
@@ -1792,13 +1858,15 @@ hipError_t launch_chains(const Bufs &B, const ParamsDev &P, int run, const RunHo
   const int nch = h.c1 - h.c0, nu = h.u1 - h.u0;
   const bool plain = P.kf_split <= 0 && P.kf_bands <= 0 && P.kf_rows <= 0;  // the order is by unit and start hit
   if (h.lds_unit && plain && nu > 0) {
-    if (h.lds_unit == kLdsUnitSmall) {
-      k_chain_units<kLdsUnitSmall, 512><<<grid_for(nu, 1, 2048), 512, 0, s>>>(B, P, run, P.n_rows);
+    const bool small = h.lds_unit == kLdsUnitSmall, many = nu >= kManyUnits;
+    if (small || many) k_chain_units<kLdsUnitSmall, 512><<<grid_for(nu, 1, 2048), 512, 0, s>>>(B, P, run, P.n_rows, -1);
+    if (!small)
+      k_chain_units<kLdsUnit, 1024><<<grid_for(nu, 1, 2048), 1024, 0, s>>>(B, P, run, P.n_rows,
+                                                                         many ? kLdsUnitSmall : -1);
+    if (small)
       k_rank_units<kLdsUnitSmall, 256><<<grid_for(nu, 1, 4096), 256, 0, s>>>(B, run, P.n_rows);
-    } else {
-      k_chain_units<kLdsUnit, 1024><<<grid_for(nu, 1, 256), 1024, 0, s>>>(B, P, run, P.n_rows);
+    else
       k_rank_units<kLdsUnit, 1024><<<grid_for(nu, 1, 512), 1024, 0, s>>>(B, run, P.n_rows);
-    }
     return hipGetLastError();
   }
   if (nch > 0) {
@@ -1834,7 +1902,7 @@ hipError_t launch_select(const Bufs &B, const ParamsDev &P, int run, const RunHo
                          hipStream_t s) {
   const int nu = h.u1 - h.u0;
   const int tg = grid_for((int64_t)h.trk_cap, kBlock, 8192);  // thread per tracklet (claims)
-  const int gg = grid_for((int64_t)h.trk_cap * kGrp, kBlock, 8192);  // lane group per tracklet
+  const int gg = grid_for((int64_t)h.trk_cap * kGrp, kBlock * 4, 8192);  // lane group per tracklet, one in four slots used
   const int64_t tiles = (h.trk_cap + kScanTile - 1) / kScanTile;
   if (h.trk_cap > 0) {
     if (!P.kf_claims) k_claim<<<tg, kBlock, 0, s>>>(B, P, run);
@@ -1848,7 +1916,16 @@ hipError_t launch_select(const Bufs &B, const ParamsDev &P, int run, const RunHo
     k_acc_apply<<<grid_for(tiles, 1, 8192), kBlock, 0, s>>>(B, run);
     if (nu > 0) k_unit_results<<<grid_for(nu, 64, 1024), 64, 0, s>>>(B, run);
   }
-  if (h.trk_cap > 0) k_output<<<gg, kBlock, 0, s>>>(B, P, run);
+  if (h.trk_cap > 0) {
+    if (h.lds_unit && nu >= kManyUnits) {
+      k_output<false><<<gg, kBlock, 0, s>>>(B, P, run);
+      k_assign_units<kLdsUnitSmall, 512><<<grid_for(nu, 1, 2048), 512, 0, s>>>(B, run, -1);
+      if (h.lds_unit > kLdsUnitSmall)
+        k_assign_units<kLdsUnit, 1024><<<grid_for(nu, 1, 2048), 1024, 0, s>>>(B, run, kLdsUnitSmall);
+    } else {
+      k_output<true><<<gg, kBlock, 0, s>>>(B, P, run);
+    }
+  }
   return hipGetLastError();
 }
 

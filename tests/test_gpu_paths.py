@@ -281,3 +281,19 @@ def test_compression_steps_inside_and_outside_the_shared_reciprocals(tpcca, row_
         ctx.phase2()
         grec, gres = ctx.get_compressed(slot, sec)
     assert np.array_equal(grec, rec) and np.array_equal(gres, res)
+
+
+@pytest.mark.parametrize("units, largest", [(255, 8192), (256, 8192), (256, 8193), (300, 40960), (256, 40961)])
+def test_runs_of_many_units(tpcca, row_x, units, largest):
+    """From 256 units on the units' chains and assignments go by two sizes of
+    blocks: units around the limits among short, empty and one-cluster ones."""
+    big = tpcgen.central_event(seed=8, n_tracks=12500, keep_truth=False)
+    sizes = [largest, 8191, 8192, min(largest, 8193), 0, 1, largest] + [300 + 7 * (u % 40) for u in range(units - 7)]
+    parts = [(u, tuple(a[:k] for a in big.unit(u % 36)[:2])) for u, k in enumerate(sizes)]
+    off = np.cumsum([0] + sizes)
+    table = np.array([(off[u], sizes[u], u // 36, u % 36) for u in range(units)], np.int64)
+    b = tpcgen.Batch(np.concatenate([p[0] for _, p in parts]), np.concatenate([p[1] for _, p in parts]), table)
+    refs = _parity.oracle_units(b, row_x)
+    with tpcca.Context(row_x) as ctx:
+        ctx.run_batch(b.cl, b.row, table)
+        _parity.compare_batch(*ctx.get_batch_results(), b, refs)
