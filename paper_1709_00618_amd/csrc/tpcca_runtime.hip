@@ -1672,11 +1672,13 @@ int tpcca_phase2(tpcca_ctx_t *c) {
   RCCHK(copy_sync(c, c->p2units.p, pu.data(), sizeof(P2Unit) * U, hipMemcpyHostToDevice));
   const P2Params q = p2_dev(c->p2params);
   const ParamsDev P = p2_prop_params(c);
-  hipError_t e = p2_launch_merge(c->B, c->P2, P, q, U, T, c->n_total, c->stream);
+  // a track won at least min_hits hits that no other has
+  const int64_t segs = std::max<int64_t>(1, std::min<int64_t>(T, c->n_total / std::max(1, P.min_hits)));
+  hipError_t e = p2_launch_merge(c->B, c->P2, P, q, U, segs, c->n_total, c->stream);
   if (e != hipSuccess) return dev_err(c, e, "second phase (merge)");
   RCCHK(copy_sync(c, &c->p2c, c->p2cnt.p, sizeof(P2Counts), hipMemcpyDeviceToHost));
   RCCHK(ensure(c, c->p2pairs, sizeof(int2) * (size_t)std::max<int64_t>(c->p2c.n_pairs, 1), 0));
-  e = p2_launch_pairs(c->B, c->P2, P, q, T, ptr<int2>(c->p2pairs), c->p2c.n_pairs, c->stream);
+  e = p2_launch_pairs(c->B, c->P2, P, q, c->p2c.n_seg, ptr<int2>(c->p2pairs), c->p2c.n_pairs, c->stream);
   if (e != hipSuccess) return dev_err(c, e, "second phase (pairs, refit)");
   RCCHK(copy_sync(c, &c->p2c, c->p2cnt.p, sizeof(P2Counts), hipMemcpyDeviceToHost));
   const size_t tmp = p2_sort_tmp_bytes(c->p2c.n_cand);
