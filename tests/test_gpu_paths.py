@@ -68,7 +68,7 @@ FIT_FORMS = [
 ]
 
 
-@pytest.mark.parametrize("tracks, sectors", [(12, 1), (700, 3), (8000, 4)])
+@pytest.mark.parametrize("tracks, sectors", [(12, 1), (700, 3), (8000, 4), (8000, 36)])
 def test_fit_forms_against_the_oracle(tpcca, torch_cuda, row_x, tracks, sectors):
     """Both forms of the fit kernel (loops for few tracklets, state machine for
     many) at tracklet counts below and above a wave each, with every block size,
