@@ -456,8 +456,10 @@ def main():
 
 
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_timeframe128.json")
-KERNEL_SOURCES = ("paper_1709_00618_amd/csrc/tpcca_kernels.hip", "paper_1709_00618_amd/csrc/tpcca_internal.h",
-                  "paper_1709_00618_amd/csrc/tpcca_kf.h", "paper_1709_00618_amd/csrc/tpcca_dev.h")
+KERNEL_SOURCES = ("paper_1709_00618_amd/csrc/tpcca_kernels.hip", "paper_1709_00618_amd/csrc/tpcca_fit.hip",
+                  "paper_1709_00618_amd/csrc/tpcca_phase2.hip", "paper_1709_00618_amd/csrc/tpcca_internal.h",
+                  "paper_1709_00618_amd/csrc/tpcca_fit.h", "paper_1709_00618_amd/csrc/tpcca_kf.h",
+                  "paper_1709_00618_amd/csrc/tpcca_dev.h")
 
 
 def kernel_source_hash():

@@ -14,6 +14,7 @@ struct RunHost {
   int32_t tile0, tile1;
   int32_t rows;  // how full the pad rows of the run's units are: a RowClass
   int32_t lds_unit;  // the run's units have at most this many hits (0: more), see unit_class
+  int32_t many;      // the run has kManyUnits units or more (a captured launch's u1 is a capacity)
 };
 
 // By mean hits in a pad row: which kernels sort the rows and search the

@@ -1858,7 +1858,7 @@ hipError_t launch_chains(const Bufs &B, const ParamsDev &P, int run, const RunHo
   const int nch = h.c1 - h.c0, nu = h.u1 - h.u0;
   const bool plain = P.kf_split <= 0 && P.kf_bands <= 0 && P.kf_rows <= 0;  // the order is by unit and start hit
   if (h.lds_unit && plain && nu > 0) {
-    const bool small = h.lds_unit == kLdsUnitSmall, many = nu >= kManyUnits;
+    const bool small = h.lds_unit == kLdsUnitSmall, many = h.many != 0;
     if (small || many) k_chain_units<kLdsUnitSmall, 512><<<grid_for(nu, 1, 2048), 512, 0, s>>>(B, P, run, P.n_rows, -1);
     if (!small)
       k_chain_units<kLdsUnit, 1024><<<grid_for(nu, 1, 2048), 1024, 0, s>>>(B, P, run, P.n_rows,
@@ -1917,7 +1917,7 @@ hipError_t launch_select(const Bufs &B, const ParamsDev &P, int run, const RunHo
     if (nu > 0) k_unit_results<<<grid_for(nu, 64, 1024), 64, 0, s>>>(B, run);
   }
   if (h.trk_cap > 0) {
-    if (h.lds_unit && nu >= kManyUnits) {
+    if (h.lds_unit && h.many) {
       k_output<false><<<gg, kBlock, 0, s>>>(B, P, run);
       k_assign_units<kLdsUnitSmall, 512><<<grid_for(nu, 1, 2048), 512, 0, s>>>(B, run, -1);
       if (h.lds_unit > kLdsUnitSmall)

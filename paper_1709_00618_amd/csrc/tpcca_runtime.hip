@@ -126,7 +126,7 @@ static void drop_graphs(tpcca_ctx *c) {
 
 static bool same_capacities(const RunHost &a, const RunHost &b) {
   return a.u1 == b.u1 && a.c1 == b.c1 && a.cl1 == b.cl1 && a.bin1 == b.bin1 && a.trk_cap == b.trk_cap &&
-         a.tile1 == b.tile1 && a.rows == b.rows && a.lds_unit == b.lds_unit;
+         a.tile1 == b.tile1 && a.rows == b.rows && a.lds_unit == b.lds_unit && a.many == b.many;
 }
 
 static int dev_err(tpcca_ctx *c, hipError_t e, const char *what) {
@@ -366,6 +366,7 @@ static RunHost make_run(tpcca_ctx *c, int u0, int u1) {
   int32_t largest = 0;
   for (int u = u0; u < u1; ++u) largest = std::max(largest, c->units[u].n);
   h.lds_unit = unit_class(u1 - u0, largest);
+  h.many = u1 - u0 >= kManyUnits ? 1 : 0;
   return h;
 }
 
@@ -1394,6 +1395,7 @@ extern "C" int tpcca_run_batch_noalloc(const tpcca_geometry_t *geo, const tpcca_
   h.tile1 = (int32_t)tiles_total;
   h.rows = row_class(U, n_total, R);
   h.lds_unit = unit_class(U, largest);
+  h.many = U >= kManyUnits ? 1 : 0;
   RunDev &rd = H.runs[0];
   rd.u0 = h.u0;
   rd.u1 = h.u1;

@@ -295,5 +295,6 @@ def test_runs_of_many_units(tpcca, row_x, units, largest):
     b = tpcgen.Batch(np.concatenate([p[0] for _, p in parts]), np.concatenate([p[1] for _, p in parts]), table)
     refs = _parity.oracle_units(b, row_x)
     with tpcca.Context(row_x) as ctx:
-        ctx.run_batch(b.cl, b.row, table)
-        _parity.compare_batch(*ctx.get_batch_results(), b, refs)
+        for graph in (False, True, True):
+            ctx.run_batch(b.cl, b.row, table, graph=graph)
+            _parity.compare_batch(*ctx.get_batch_results(), b, refs)
