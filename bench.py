@@ -521,7 +521,7 @@ def summarize_profile(trace_dir, fetch_dir, write_dir, command, sq_dir=None, out
 
     def tf_end(ids_names):
         # the time-frame replays come first; each ends with k_output
-        outs = sorted(i for i, n in ids_names if short(n) == "k_output")
+        outs = sorted(i for i, n in ids_names if short(n).split("<")[0] == "k_output")
         return outs[tf_n - 1] if len(outs) >= tf_n else max(i for i, _ in ids_names)
 
     # kernel trace: split at the last dispatch of the time-frame replays
