@@ -20,8 +20,9 @@ struct RunHost {
 // By mean hits in a pad row: which kernels sort the rows and search the
 // neighbours.  The lines lie where the two kernels on their sides meet on time
 // frames of few events (45 hits in a row per event; us):
-//   neighbours, wave per tile / block per tile: 21 / 24 at 90 hits, 64 / 33 at
-//     140 (a wave takes the 64-hit lots of its tile one after the other);
+//   neighbours, wave per tile / block per tile: 21 / 24 at 90 hits, 46 / 39 at
+//     180, 161 / 132 at 720 (a wave takes the 64-hit lots of its tile one after
+//     the other);
 //   row sort, wave per row / block of 256: 18 / 30 at 270 hits, 55 / 34 at 360
 //     (rows above 512 hits leave the wave form);
 //   row sort, block of 256 / staged in LDS: at 1024 hits a row begins to fill

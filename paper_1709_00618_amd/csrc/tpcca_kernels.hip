@@ -804,8 +804,9 @@ __global__ __launch_bounds__(kT, 7) void k_links(Bufs B, ParamsDev P, int run) {
 // with the neighbours of 64 hits at a time in its own part of the LDS, and no
 // barrier.  With 46 hits in a row (64 minimum-bias events) a block of 256
 // threads per tile keeps one lane in six busy and waits three times for its
-// slowest wave: 1145 us, against 610 us here.  Bound by instruction issue (216
-// million vector instructions, 65% of the time at four cycles each).
+// slowest wave: 1145 us, against 457 us here (538 with staged hits and staged
+// bin starts under one condition, in 95 registers instead of 68; 613 with room
+// for 128 bins only).  Bound by instruction issue.
 template <int kNbr, int kBins>
 __global__ __launch_bounds__(256, 5) void k_links_waves(Bufs B, ParamsDev P, int run) {
   __shared__ float2 s_up_[4][kNbr + 1], s_dn_[4][kNbr + 1];
@@ -860,12 +861,14 @@ __global__ __launch_bounds__(256, 5) void k_links_waves(Bufs B, ParamsDev P, int
       const int dbhi = __builtin_amdgcn_readfirstlane(zbin(td, zhi + ldz + tpad));
       const int ua = B.binbeg[tu.bin0 + ublo], ue_ = B.binbeg[tu.bin0 + ubhi + 1];
       const int da = B.binbeg[td.bin0 + dblo], de_ = B.binbeg[td.bin0 + dbhi + 1];
-      const bool lds = (ue_ - ua) <= kNbr && (de_ - da) <= kNbr && (ubhi - ublo + 2) <= kBins &&
-                       (dbhi - dblo + 2) <= kBins;
+      const bool lds = (ue_ - ua) <= kNbr && (de_ - da) <= kNbr;
+      const bool lds_bins = (ubhi - ublo + 2) <= kBins && (dbhi - dblo + 2) <= kBins;
       wave_lds_order();  // the neighbours of the lot before have been read
       if (lds) {
         for (int q = lane; q < ue_ - ua; q += 64) s_up[q] = B.yz[ua + q];
         for (int q = lane; q < de_ - da; q += 64) s_dn[q] = B.yz[da + q];
+      }
+      if (lds_bins) {
         for (int q = lane; q <= ubhi - ublo + 1; q += 64)
           s_bup[q] = (uint16_t)(B.binbeg[tu.bin0 + ublo + q] - ua);
         for (int q = lane; q <= dbhi - dblo + 1; q += 64)
@@ -876,14 +879,18 @@ __global__ __launch_bounds__(256, 5) void k_links_waves(Bufs B, ParamsDev P, int
         const float pad = 1e-3f + 1e-6f * fabsf(h.y);
         const int bu0 = zbin(tu, h.y - luz - pad), bu1 = zbin(tu, h.y + luz + pad);
         const int bd0 = zbin(td, h.y - ldz - pad), bd1 = zbin(td, h.y + ldz + pad);
+        int ub, ue, db, de;
+        if (lds_bins) {
+          ub = ua + s_bup[bu0 - ublo], ue = ua + s_bup[bu1 + 1 - ublo];
+          db = da + s_bdn[bd0 - dblo], de = da + s_bdn[bd1 + 1 - dblo];
+        } else {
+          ub = B.binbeg[tu.bin0 + bu0], ue = B.binbeg[tu.bin0 + bu1 + 1];
+          db = B.binbeg[td.bin0 + bd0], de = B.binbeg[td.bin0 + bd1 + 1];
+        }
         LinkBest b;
         if (lds) {
-          const int ub = ua + s_bup[bu0 - ublo], ue = ua + s_bup[bu1 + 1 - ublo];
-          const int db = da + s_bdn[bd0 - dblo], de = da + s_bdn[bd1 + 1 - dblo];
           b = link_hit_lds(B, h, luy, luz, ldy, ldz, w, ub, ue, db, de, s_up, s_dn, ua, da);
         } else {
-          const int ub = B.binbeg[tu.bin0 + bu0], ue = B.binbeg[tu.bin0 + bu1 + 1];
-          const int db = B.binbeg[td.bin0 + bd0], de = B.binbeg[td.bin0 + bd1 + 1];
           b = link_all_pairs<false>(B, h, luy, luz, ldy, ldz, w, ub, ue, db, de, nullptr, nullptr, 0, 0);
         }
         const bool ok = b.u >= 0 && b.c2 <= P.link_chi2;
@@ -1816,7 +1823,7 @@ hipError_t launch_links(const Bufs &B, const ParamsDev &P, int run, const RunHos
     g = (g + 7) & ~7;  // a multiple of the 8 XCDs
     const int tile = link_tile_of(P);
     if (h.rows == kRowsSparse && P.link_tile <= 0 && P.link_stage == 0) {
-      k_links_waves<256, 128><<<(grid_for(nt, 4, 256 * 32) + 7) & ~7, 256, 0, s>>>(B, P, run);
+      k_links_waves<256, 256><<<(grid_for(nt, 4, 256 * 32) + 7) & ~7, 256, 0, s>>>(B, P, run);
       return hipGetLastError();
     }
 #define TPCCA_LINKS(V, T) k_links<V, T><<<g, T, 0, s>>>(B, P, run)
