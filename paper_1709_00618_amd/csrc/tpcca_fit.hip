@@ -73,9 +73,11 @@ __device__ __forceinline__ void few_share(int n, int &lo, int &hi) {
 // there is: with 104 to a wave (64 minimum-bias events) claims of 64 after the
 // first 64 went to two waves in three, and the fit took 2.76 ms; equal shares
 // take 2.50, of 85 (frame of 32 events) 2.33 instead of 2.87.  With more, claims
-// balance better: at 171 (64 events) 4.64 ms, 4.82 with claims of up to four
-// times what is left per wave, 5.67 with a third of it; at 334 (128 events) 8.24,
-// 8.39 and 9.15.
+// balance better: whole passes of two frames in flight and of one alone, claims
+// against equal shares, take 6.58 and 7.05 ms against 6.71 and 7.09 at 179 to a
+// wave (frames of 80 events), 7.92 and 8.55 against 8.45 and 8.81 at 215 (96).
+// Claims of at most half of what is left per wave, instead of four times that:
+// 128 events alone 10.90 -> 10.75 ms, two in flight 10.08 -> 10.19 per frame.
 constexpr int kEqualShare = 128;
 struct Pool {
   int next = 0, end = 0;  // claimed, not yet started
@@ -102,18 +104,18 @@ __device__ __forceinline__ Pool pool_start(const ParamsDev &P, int n) {
 }
 
 // Claims the next tracklets of the wave's slice with one atomic per wave:
-// kf_pool neighbouring ones while many remain, at most half of what is left per
-// wave (judged from this wave's previous claim), but never fewer than the idle
-// lanes, so that at the end no wave holds a private backlog.  With slices per
-// XCD (kf_xcd), the waves of an XCD drain its slice first and then help with
-// the following ones.
+// kf_pool neighbouring ones while many remain; in the last stretch (less than
+// a quarter pool per wave left, judged from this wave's previous claim) fewer,
+// but never fewer than the idle lanes, so that at the end no wave holds a
+// private backlog.  With slices per XCD (kf_xcd), the waves of an XCD drain
+// its slice first and then help with the following ones.
 __device__ __forceinline__ void pool_claim(const ParamsDev &P, Pool &p, int32_t *counter, int n, int n_idle,
                                            int lane) {
   const int nsl = P.kf_xcd ? kXcds : 1;
   int lo = 0, hi = n;
   if (nsl > 1) pool_slice(n, nsl, p.part, lo, hi);
-  const int nw = max(1, (int)((gridDim.x * blockDim.x) >> 6) / nsl);  // the slice's waves
-  const int want = max(n_idle, min(P.kf_pool, ((hi - lo) - p.seen) / (2 * nw)));
+  const int nw = (int)((gridDim.x * blockDim.x) >> 6);
+  const int want = max(n_idle, min(P.kf_pool, 4 * (((hi - lo) - p.seen) / nw)));
   int got = 0;
   if (p.base < hi - lo) {
     if (lane == 0) got = atomicAdd(&counter[p.part], want);
