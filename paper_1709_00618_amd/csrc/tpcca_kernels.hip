@@ -862,7 +862,10 @@ __global__ __launch_bounds__(256, 5) void k_links_waves(Bufs B, ParamsDev P, int
       const int ua = B.binbeg[tu.bin0 + ublo], ue_ = B.binbeg[tu.bin0 + ubhi + 1];
       const int da = B.binbeg[td.bin0 + dblo], de_ = B.binbeg[td.bin0 + dbhi + 1];
       const bool lds = (ue_ - ua) <= kNbr && (de_ - da) <= kNbr;
-      const bool lds_bins = (ubhi - ublo + 2) <= kBins && (dbhi - dblo + 2) <= kBins;
+      // staged bin starts are 16-bit distances from ua / da: the spans have to
+      // fit as well (few bins may hold a crowded row of more than 65535 hits)
+      const bool lds_bins = (ubhi - ublo + 2) <= kBins && (dbhi - dblo + 2) <= kBins &&
+                            max(ue_ - ua, de_ - da) <= 0xFFFF;
       wave_lds_order();  // the neighbours of the lot before have been read
       if (lds) {
         for (int q = lane; q < ue_ - ua; q += 64) s_up[q] = B.yz[ua + q];
