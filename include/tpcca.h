@@ -161,8 +161,7 @@ int tpcca_destroy(tpcca_ctx_t *ctx);
 int tpcca_reset(tpcca_ctx_t *ctx);
 
 /* Append unit (slot, sector) with n clusters.  flags = TPCCA_MEM_HOST: the
-   clusters are copied (asynchronously from a pinned staging buffer) and the
-   caller may reuse its buffers on return.  TPCCA_MEM_DEVICE: the pointers are
+   clusters have been copied on return and the caller may reuse its buffers.  TPCCA_MEM_DEVICE: the pointers are
    device addresses read in place; they must stay valid until tpcca_sync().
    Validation of rows and coordinates happens on the device; a bad cluster
    makes the next stage call's tpcca_sync() return EINVAL.  A (slot, sector)
@@ -206,8 +205,10 @@ int tpcca_get_assignment(tpcca_ctx_t *ctx, int32_t slot, int32_t sector, int32_t
 
 /* Reset, load every unit of the batch and run all stages on all of them in
    one launch per kernel (TPCCA_BATCH_GRAPH: as a replayed HIP graph of
-   persistent kernels whose work counts live in device memory).  Does not
-   synchronise.  Errors: EINVAL, ENOMEM, EDEVICE. */
+   persistent kernels whose work counts live in device memory).  Returns while
+   the stages run; host input (TPCCA_MEM_HOST) has been copied by then and may
+   be reused, device input is read in place and must stay valid until
+   tpcca_sync().  Errors: EINVAL, ENOMEM, EDEVICE. */
 int tpcca_run_batch(tpcca_ctx_t *ctx, const tpcca_batch_t *batch);
 
 /* Copy the whole batch's results to the host: units (n_units entries),

@@ -63,6 +63,7 @@ struct tpcca_ctx {
   char *tables_pin = nullptr;  // pinned copy of the tables under way to the device
   size_t tables_pin_bytes = 0;
   hipEvent_t tables_sent = nullptr;  // its copies have been made
+  hipEvent_t input_read = nullptr;   // the copies of a batch's host input have been made
   std::vector<int> pending_runs;  // runs launched since the last sync
 
   // device buffers
@@ -677,6 +678,11 @@ int tpcca_create(const tpcca_geometry_t *geo, const tpcca_params_t *params, int 
     c->own_stream = true;
   }
   for (int k = 0; k < 7; ++k) hipEventCreate(&c->ev[k]);
+  e = hipEventCreateWithFlags(&c->input_read, hipEventDisableTiming);
+  if (e != hipSuccess) {
+    tpcca_destroy(c);
+    return TPCCA_EDEVICE;
+  }
   c->unit_chunk0.push_back(0);
   int rc = ensure(c, c->row_x_d, sizeof(float) * c->R, 0);
   if (rc == TPCCA_OK) rc = copy_sync(c, c->row_x_d.p, c->row_x.data(), sizeof(float) * c->R, hipMemcpyHostToDevice);
@@ -715,6 +721,7 @@ int tpcca_destroy(tpcca_ctx_t *c) {
     if (c->ev[k]) hipEventDestroy(c->ev[k]);
   if (c->tables_pin) hipHostFree(c->tables_pin);
   if (c->tables_sent) hipEventDestroy(c->tables_sent);
+  if (c->input_read) hipEventDestroy(c->input_read);
   if (c->own_stream && c->stream) hipStreamDestroy(c->stream);
   delete c;
   return TPCCA_OK;
@@ -920,7 +927,9 @@ static int64_t bucket(int64_t v) {
   return b;
 }
 
-int tpcca_run_batch(tpcca_ctx_t *c, const tpcca_batch_t *bt) {
+// Queues a batch; *copying: input_read marks the end of the copies from the
+// caller's host input.
+static int queue_batch(tpcca_ctx_t *c, const tpcca_batch_t *bt, bool *copying) {
   if (!c || !bt || bt->n_units < 0) return TPCCA_EINVAL;
   if (bt->n_units > 0 && (!bt->slot || !bt->sector || !bt->begin || !bt->n)) return TPCCA_EINVAL;
   hipSetDevice(c->device);
@@ -947,9 +956,16 @@ int tpcca_run_batch(tpcca_ctx_t *c, const tpcca_batch_t *bt) {
     const int64_t span = hi - lo;
     if ((rc = ensure(c, c->in_cl, (size_t)span * sizeof(float4), 0)) != TPCCA_OK) return rc;
     if ((rc = ensure(c, c->in_row, (size_t)span, 0)) != TPCCA_OK) return rc;
-    HIPCHK(c, hipMemcpyAsync(c->in_cl.p, bt->cl + lo, (size_t)span * sizeof(float4),
-                             hipMemcpyHostToDevice, c->stream));
-    HIPCHK(c, hipMemcpyAsync(c->in_row.p, bt->row + lo, (size_t)span, hipMemcpyHostToDevice, c->stream));
+    hipError_t e = hipMemcpyAsync(c->in_cl.p, bt->cl + lo, (size_t)span * sizeof(float4),
+                                  hipMemcpyHostToDevice, c->stream);
+    if (e == hipSuccess)
+      e = hipMemcpyAsync(c->in_row.p, bt->row + lo, (size_t)span, hipMemcpyHostToDevice, c->stream);
+    if (e == hipSuccess) e = hipEventRecord(c->input_read, c->stream);
+    if (e != hipSuccess) {
+      hipStreamSynchronize(c->stream);  // what was queued has been read as well
+      return dev_err(c, e, "hipMemcpyAsync(batch input)");
+    }
+    *copying = true;
     cl_base = reinterpret_cast<const tpcca_cluster_t *>(ptr<float4>(c->in_cl)) - lo;
     row_base = ptr<uint8_t>(c->in_row) - lo;
   }
@@ -1067,6 +1083,18 @@ int tpcca_run_batch(tpcca_ctx_t *c, const tpcca_batch_t *bt) {
   }
   c->have_times = ge->timing;
   return TPCCA_OK;
+}
+
+int tpcca_run_batch(tpcca_ctx_t *c, const tpcca_batch_t *bt) {
+  bool copying = false;
+  const int rc = queue_batch(c, bt, &copying);
+  // the caller may reuse its input on return; the launches queued behind the
+  // copies overlap the wait
+  if (copying) {
+    const hipError_t e = hipEventSynchronize(c->input_read);
+    if (rc == TPCCA_OK && e != hipSuccess) return dev_err(c, e, "batch input");
+  }
+  return rc;
 }
 
 int tpcca_batch_totals(tpcca_ctx_t *c, int32_t *n_units, int64_t *n_clusters, int64_t *n_tracks,
