@@ -149,8 +149,9 @@ __device__ __forceinline__ int4 load16(const void *p) {
 template <int kQ>
 __device__ __forceinline__ int kf_search(const Bufs &B, const ParamsDev &P, const RowTab &t,
                                          const KState &s, float zr, unsigned int &cands, float2 &bc) {
-  // with cluster variances the roots' arguments are in kf_sqrt's range
-  const bool mid = P.ery >= 0x1p-96f && P.erz >= 0x1p-96f;
+  // with cluster variances the roots' arguments are in kf_sqrt's range (what a
+  // covariance slightly below zero leaves of a variance is 2^-24 of it or more)
+  const bool mid = P.ery >= 0x1p-70f && P.erz >= 0x1p-70f;
   const float vy = s.C[0] + P.ery, vz = s.C[2] + P.erz;
   float wy = P.nsig * (mid ? kf_sqrt(vy) : sqrtf(vy));
   float wz = P.nsig * (mid ? kf_sqrt(vz) : sqrtf(vz));
@@ -748,6 +749,7 @@ __device__ __forceinline__ void fit_many(const Bufs &B, const ParamsDev &P, RunD
   int n1 = 0, nh = 0, j = 0;
   float chi2 = 0.0f;
   KState st{};
+  st.p[2] = 0.5f;  // a lane that never starts asks for no general division
   for (;;) {
     const unsigned long long idle = __ballot(state == kFree);
     if (idle) {

@@ -88,6 +88,7 @@ struct ParamsDev {
   int32_t max_miss, min_hits, own_pct;
   float inflate;
   int32_t hits_per_bin;
+  float tiny;  // below this |s0 + s1| a step takes the general divisions and roots (tpcca_kf.h)
   // schedule (no effect on results)
   int32_t kf_pool;
   int32_t kf_blocks_per_cu;

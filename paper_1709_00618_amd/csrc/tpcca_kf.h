@@ -28,6 +28,8 @@ namespace tpcca {
 //   root        v_sqrt_f32 (1 ulp) corrected once by its exact residual over
 //               twice the root; equal to the correctly rounded one for every
 //               float from 2^-96 to 2^120 (all checked), 0 and infinity.
+// Checked on the device by tests/test_gpu_arithmetic.py.  Where an operand may
+// lie outside, the callers below take the general operations.
 struct KRecip {
   float d, r;
 };
@@ -58,40 +60,66 @@ struct KState {
 // arc length (signed like dx) is the chord times the Maclaurin series of
 // asin(u)/u to u^8, u = chord |k| / 2.  The Jacobian is the simplified one
 // that drops the curvature term of the arc length.  C <- F C F^T.
+//
+// What a step takes of the two directions sin phi = s0, s1 and of dx: the
+// displacement dy, the chord and its square, the Jacobian's a and b, and dy
+// over the chord.  In the short forms above or, kShort false, by the general
+// division and root.
+struct KGeo {
+  float dy, ch2, chs, a, b, dych;
+};
+template <bool kShort>
+__device__ __forceinline__ KGeo kf_geometry(const ParamsDev &P, float dx, float s0, float s1) {
+  auto root = [](float x) { return kShort ? kf_sqrt(x) : sqrtf(x); };
+  auto div = [](float n, const KRecip &k) { return kShort ? kf_div(n, k) : n / k.d; };
+  KGeo q;
+  const float c0 = root(__builtin_fmaf(-s0, s0, 1.0f));
+  const float c1 = root(__builtin_fmaf(-s1, s1, 1.0f));
+  const KRecip rc0 = kf_recip(c0), rc1 = kf_recip(c1), rcc = kf_recip(c0 + c1);
+  const float tt = div(s0 + s1, rcc);
+  q.dy = dx * tt;
+  q.ch2 = __builtin_fmaf(q.dy, q.dy, dx * dx);
+  const float ch = root(q.ch2);
+  q.chs = dx < 0.0f ? -ch : ch;
+  q.a = div(dx * (2.0f + tt * (div(s0, rc0) + div(s1, rc1))), rcc);
+  q.b = div(dx * P.kB * dx * (1.0f + div(tt * s1, rc1)), rcc);
+  q.dych = div(q.dy, kf_recip(q.chs));
+  return q;
+}
+
 // The step itself, for a caller that has no use for the state once the track
 // turned back (|sin phi| beyond the limit, where the state ends up undefined):
 // without a way round it, the new state takes the old one's registers.
+//
+// Where dx and kB keep the short forms exact (P.tiny), what is left to look at is
+// s0 + s1 (c0 and c1 are 0, NaN or 2^-12 to 1): from 2^-60 on, dy and its
+// quotient lie above 2^-92, and quotients of a smaller s0 or s1 only enter sums
+// with 1 or 2.  Below it the wave takes the general forms, which give its other
+// lanes the same.  One compare: a lone wave's time goes by its instructions.
 __device__ __forceinline__ bool kf_step(const ParamsDev &P, KState &s, float x1) {
   const float dx = x1 - s.x;
   const float kk = P.kB * s.p[4];
   const float s0 = s.p[2];
   const float s1 = __builtin_fmaf(kk, dx, s0);
-  const float c0 = kf_sqrt(__builtin_fmaf(-s0, s0, 1.0f));
-  const float c1 = kf_sqrt(__builtin_fmaf(-s1, s1, 1.0f));
-  const KRecip rc0 = kf_recip(c0), rc1 = kf_recip(c1), rcc = kf_recip(c0 + c1);
-  const float tt = kf_div(s0 + s1, rcc);
-  const float dy = dx * tt;
-  const float ch2 = __builtin_fmaf(dy, dy, dx * dx);
-  const float ch = kf_sqrt(ch2);
-  const float chs = dx < 0.0f ? -ch : ch;
-  const float u2 = ch2 * kk * kk * 0.25f;
+  KGeo q = kf_geometry<true>(P, dx, s0, s1);
+  if (__builtin_expect(__ballot(fabsf(s0 + s1) < P.tiny) != 0ull, 0)) q = kf_geometry<false>(P, dx, s0, s1);
+  const float u2 = q.ch2 * kk * kk * 0.25f;
   float h = (float)(35.0 / 1152.0);
   h = __builtin_fmaf(u2, h, (float)(5.0 / 112.0));
   h = __builtin_fmaf(u2, h, (float)(3.0 / 40.0));
   h = __builtin_fmaf(u2, h, (float)(1.0 / 6.0));
   h = __builtin_fmaf(u2, h, 1.0f);
-  const float dS = chs * h;
+  const float dS = q.chs * h;
   const float t = s.p[3];
 
-  const float a = kf_div(dx * (2.0f + tt * (kf_div(s0, rc0) + kf_div(s1, rc1))), rcc);
-  const float b = kf_div(dx * P.kB * dx * (1.0f + kf_div(tt * s1, rc1)), rcc);
-  const float g = ch > 0.0f ? t * kf_div(dy, kf_recip(chs)) : 0.0f;
+  const float a = q.a, b = q.b;
+  const float g = fabsf(q.chs) > 0.0f ? t * q.dych : 0.0f;
   const float cz = g * a;
   const float dzq = g * b;
   const float e = dS;
   const float f = P.kB * dx;
 
-  s.p[0] = s.p[0] + dy;
+  s.p[0] = s.p[0] + q.dy;
   s.p[1] = s.p[1] + t * dS;
   s.p[2] = s1;
   s.x = x1;
@@ -138,6 +166,14 @@ __device__ __forceinline__ bool kf_propagate(const ParamsDev &P, KState &s, floa
   return kf_step(P, s, x1);
 }
 
+// 1 / det.  The short form is exact for 2^-126 to 2^126 and gives no normal
+// number outside (checked for every float): there the wave divides.
+__device__ __forceinline__ float kf_inverse(float det) {
+  float inv = kf_div(1.0f, kf_recip(det));
+  if (__builtin_expect(__ballot(!__builtin_amdgcn_classf(inv, 0x108)) != 0ull, 0)) inv = 1.0f / det;  // +-normal
+  return inv;
+}
+
 // A 2-D measurement against the state: residual, inverse of S = C_yz + R and
 // chi2.  The test of a searched hit and the update with it share it.  Fails
 // (its values undefined) unless det S > 0.
@@ -151,7 +187,7 @@ __device__ __forceinline__ bool kf_meas(const ParamsDev &P, const KState &s, flo
   const float s10 = s.C[1];
   const float s11 = s.C[2] + P.erz;
   const float det = s00 * s11 - s10 * s10;
-  const float inv = kf_div(1.0f, kf_recip(det));
+  const float inv = kf_inverse(det);
   m.i00 = s11 * inv;
   m.i10 = -s10 * inv;
   m.i11 = s00 * inv;

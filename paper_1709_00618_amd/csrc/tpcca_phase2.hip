@@ -92,6 +92,15 @@ __device__ __forceinline__ bool p2_rotate(float max_sin, float cs, float sn, KSt
   return true;
 }
 
+// A step from or to a plane that is no pad row (a row of another sector's frame):
+// unless dx lies in the rows' range, 2^-20 to 2^21, the wave takes the general
+// operations.
+__device__ __forceinline__ bool p2_propagate(ParamsDev P, KState &st, float x1) {
+  constexpr uint32_t lo = (127u - 20u) << 23, hi = (127u + 21u) << 23;
+  if (__ballot(__float_as_uint(fabsf(x1 - st.x)) - lo > hi - lo) != 0ull) P.tiny = __builtin_inff();
+  return kf_propagate(P, st, x1);
+}
+
 __device__ __forceinline__ int p2_ci(int i, int j) { return i >= j ? i * (i + 1) / 2 + j : j * (j + 1) / 2 + i; }
 
 // d^T (C1 + C2)^-1 d: Cholesky row by row, forward substitution, sum of
@@ -590,7 +599,7 @@ __global__ __launch_bounds__(256) void k_p2_pair_eval(Bufs B, P2Bufs Q, ParamsDe
     for (int j = 0; j < 5; ++j) sa.p[j] = oa.p[j];
 #pragma unroll
     for (int j = 0; j < 15; ++j) sa.C[j] = oa.C[j];
-    if (!kf_propagate(P, sa, sb.x)) continue;
+    if (!p2_propagate(P, sa, sb.x)) continue;
     float d[5];
     d[0] = sb.p[0] - sa.p[0];
     d[1] = (zrB - zrA) - sa.p[1];
@@ -940,7 +949,7 @@ __global__ __launch_bounds__(64) void k_p2_refit(Bufs B, P2Bufs Q, ParamsDev P, 
       if (j > 0) nxt = Q.hrec[hb + j - 1];  // the next record's load overlaps this step
       const int r = __float_as_int(c.z);
       float c2;
-      if ((nh > 0 && !kf_propagate(P, st, s_rx[r])) || !kf_update(P, st, c.x, c.y - zr, c2)) {
+      if ((nh > 0 && !p2_propagate(P, st, s_rx[r])) || !kf_update(P, st, c.x, c.y - zr, c2)) {
         p2_final_failed(Q, f);
         phase = kFree;
       } else {
@@ -951,7 +960,7 @@ __global__ __launch_bounds__(64) void k_p2_refit(Bufs B, P2Bufs Q, ParamsDev P, 
       }
     } else if (phase == kAxis) {
       const float xk = (x0 * (float)(N - kd)) / (float)N;
-      if (!kf_propagate(P, st, xk)) {
+      if (!p2_propagate(P, st, xk)) {
         tpcca_final_t &o = Q.finals[f];
         o.z0 = 0.0f;
         o.t0 = 0.0f;

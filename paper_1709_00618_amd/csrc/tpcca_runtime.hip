@@ -568,9 +568,20 @@ static int load_unit(tpcca_ctx *c, int32_t slot, int32_t sector, const tpcca_clu
   return TPCCA_OK;
 }
 
+// Whether every step between rows, and kB, keep the short forms of kf_step
+// exact: steps between 2^-20 and 2^21 in size and kB 0 or between 2^-30 and 2^30
+// leave dx and dx^2 kB above 2^-70.
+static bool mid_range(const float *row_x, int R, float kB) {
+  bool ok = kB == 0.0f || (std::fabs(kB) >= 0x1p-30f && std::fabs(kB) <= 0x1p30f);
+  for (int r = 0; r < R; ++r)
+    ok = ok && std::fabs(row_x[r]) <= 0x1p20f && (r == 0 || row_x[r] - row_x[r - 1] >= 0x1p-20f);
+  return ok;
+}
+
 // Device copy of the parameters with the default launch schedule.
-static ParamsDev params_dev(const tpcca_params_t &p) {
+static ParamsDev params_dev(const tpcca_geometry_t &geo, const tpcca_params_t &p) {
   ParamsDev P{};
+  P.tiny = mid_range(geo.row_x, geo.n_rows, p.kB) ? 0x1p-60f : INFINITY;
   P.n_rows = p.n_rows;
   P.wy = p.link_wy;
   P.wz = p.link_wz;
@@ -664,7 +675,7 @@ int tpcca_create(const tpcca_geometry_t *geo, const tpcca_params_t *params, int 
   c->R = geo->n_rows;
   c->n_sectors = geo->n_sectors;
   c->row_x.assign(geo->row_x, geo->row_x + geo->n_rows);
-  c->P = params_dev(*params);
+  c->P = params_dev(*geo, *params);
   tpcca_phase2_params_default(&c->p2params);
   std::lock_guard<std::recursive_mutex> lock(tpcca::device_ops_lock());
   if (hip_stream) {
@@ -1346,7 +1357,7 @@ extern "C" int tpcca_run_batch_noalloc(const tpcca_geometry_t *geo, const tpcca_
   const int U = bt->n_units;
   if (U > 0 && (!bt->slot || !bt->sector || !bt->begin || !bt->n || !units)) return TPCCA_EINVAL;
   const int R = geo->n_rows;
-  const ParamsDev P = params_dev(*params);
+  const ParamsDev P = params_dev(*geo, *params);
   // capacities, exactly as a context reserves them for these units
   int64_t n_total = 0, bins_total = 0, trk_total = 0, tiles_total = 0, n_chunks = 0;
   for (int u = 0; u < U; ++u) {

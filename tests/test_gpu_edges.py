@@ -78,3 +78,48 @@ def test_host_input_may_be_overwritten_after_run_batch(tpcca, torch_cuda, row_x,
             row[:] = 255
             cl[:] = np.nan
             assert [a.tobytes() for a in ctx.get_batch_results()] == want
+
+
+# cluster variances whose determinant leaves 2^-120 .. 2^120 (its reciprocal, too),
+# a field of 1e-36, directions of 1e-37, rows 1e-18 apart (no second phase: it
+# tells rows by their x)
+FAR = [
+    dict(err2_y=6e-20, err2_z=6e-20, seed_c22=6e-22, seed_c33=6e-22, seed_c44=6e-19, pick_nsig=1e12, pick_chi2=1e22,
+         refit_inflate=1.0),
+    dict(err2_y=5e17, err2_z=1e20, seed_c22=1e16, seed_c33=1e17, seed_c44=1e18, pick_nsig=1e-8, pick_chi2=1e-10,
+         refit_inflate=1.0),
+    dict(err2_y=1e18, err2_z=1e20, seed_c22=1e16, seed_c33=1e17, seed_c44=1e18, pick_nsig=1e-8, pick_chi2=1e-10,
+         refit_inflate=1.0),
+    dict(kB=1e-36), dict(y=1e-36), dict(y=1e-34, kB=0.0), dict(x=1e-18),
+]
+
+
+@pytest.mark.parametrize("far", FAR)
+def test_fits_outside_the_range_of_the_short_quotients(tpcca, row_x, far):
+    """Every fit form and the compression where quotients and roots leave the range
+    in which their short forms are exact, against the oracle."""
+    b = tpcgen.one_sector(seed=21)
+    cl, row, slot, sec, _ = b.unit(0)
+    over = {k: v for k, v in far.items() if k not in "xy"}
+    rx = (row_x * np.float32(far.get("x", 1.0))).astype(np.float32)
+    cl = cl.copy()
+    cl[:, 1] *= np.float32(far.get("y", 1.0))
+    cl[:, 1:3] *= np.float32(far.get("x", 1.0))
+    cl[:, 0] = rx[row]
+    params = oracle.default_params(**over)
+    ref = oracle.run_sector(cl, row, rx, params)
+    assert ref.n_tracks >= 20
+    seg, hb, hits = oracle.segments_of([ref])
+    rec, res = oracle.compress(cl, row, rx, seg, hb, hits, params=params)
+    for knobs in ({}, {"fit_xcd_slices": 1}, {"fit_rows": 256}):
+        with tpcca.Context(rx, params=tpcca.params_default(**over)) as ctx:
+            ctx.set_tuning(**knobs)
+            ctx.load_sector(slot, sec, cl, row)
+            ctx.run_all()
+            ctx.sync()
+            _parity.compare_unit_stagewise(ctx, slot, sec, cl, row, ref)
+            if "x" in far:
+                continue
+            ctx.phase2()
+            grec, gres = ctx.get_compressed(slot, sec)
+        assert np.array_equal(grec, rec) and np.array_equal(gres, res)
