@@ -1822,11 +1822,12 @@ hipError_t launch_links(const Bufs &B, const ParamsDev &P, int run, const RunHos
                         hipStream_t s) {
   const int nt = h.tile1 - h.tile0;
   if (nt > 0) {
-    int g = grid_for(nt, 1, 256 * (P.link_blocks_per_cu > 0 ? P.link_blocks_per_cu : 32));
-    g = (g + 7) & ~7;  // a multiple of the 8 XCDs
+    const int cap = 256 * (P.link_blocks_per_cu > 0 ? P.link_blocks_per_cu : 32);
+    // a multiple of the 8 XCDs
+    const int g = (grid_for(nt, 1, cap) + 7) & ~7;
     const int tile = link_tile_of(P);
     if (h.rows == kRowsSparse && P.link_tile <= 0 && P.link_stage == 0) {
-      k_links_waves<256, 256><<<(grid_for(nt, 4, 256 * 32) + 7) & ~7, 256, 0, s>>>(B, P, run);
+      k_links_waves<256, 256><<<(grid_for(nt, 4, cap) + 7) & ~7, 256, 0, s>>>(B, P, run);
       return hipGetLastError();
     }
 #define TPCCA_LINKS(V, T) k_links<V, T><<<g, T, 0, s>>>(B, P, run)

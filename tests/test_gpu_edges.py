@@ -1,6 +1,8 @@
 """GPU parity at the edges of what single kernels and host paths hold: values
 that outgrow a narrower type, buffers that change under a queued copy, knobs
 and numbers out of the usual range."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -123,3 +125,48 @@ def test_fits_outside_the_range_of_the_short_quotients(tpcca, row_x, far):
             ctx.phase2()
             grec, gres = ctx.get_compressed(slot, sec)
         assert np.array_equal(grec, rec) and np.array_equal(gres, res)
+
+
+class KernelNode(ctypes.Structure):  # hipKernelNodeParams
+    _fields_ = [("block", ctypes.c_uint32 * 3), ("extra", ctypes.c_void_p), ("func", ctypes.c_void_p),
+                ("grid", ctypes.c_uint32 * 3), ("args", ctypes.POINTER(ctypes.c_void_p)), ("shared", ctypes.c_uint32)]
+
+
+def _launches(tpcca, stream, call, look=None):
+    """The kernels that `call` queues on the stream, captured in a graph and not run:
+    (function, grid) each, or what `look` makes of their nodes."""
+    hip = tpcca.lib()  # the runtime that the library is linked to
+    vp = ctypes.c_void_p
+    graph = vp()
+    assert hip.hipStreamBeginCapture(vp(stream), 2) == 0  # relaxed: the test is the only user
+    try:
+        call()
+    finally:
+        assert hip.hipStreamEndCapture(vp(stream), ctypes.byref(graph)) == 0
+    n = ctypes.c_size_t()
+    assert hip.hipGraphGetNodes(graph, None, ctypes.byref(n)) == 0
+    nodes = (vp * n.value)()
+    assert hip.hipGraphGetNodes(graph, nodes, ctypes.byref(n)) == 0
+    out = []
+    for node in nodes:
+        k = KernelNode()
+        assert hip.hipGraphKernelNodeGetParams(vp(node), ctypes.byref(k)) == 0
+        out.append(look(k) if look else (k.func, tuple(k.grid)))
+    assert hip.hipGraphDestroy(graph) == 0
+    return out
+
+
+@pytest.mark.parametrize("per_cu, grid", [(0, 1456), (1, 256), (3, 768), (32, 1456)])
+def test_link_blocks_per_cu_holds_for_sparse_rows(tpcca, torch_cuda, row_x, per_cu, grid):
+    """The resident blocks per CU that were asked for, also in the neighbour search by
+    waves: 36 short units (161 tile slots each, four to a block of the default)."""
+    stream = torch_cuda.cuda.Stream().cuda_stream
+    b = tpcgen.one_sector(seed=2)
+    with tpcca.Context(row_x, stream=stream) as ctx:
+        ctx.set_tuning(link_blocks_per_cu=per_cu)
+        for slot in (0, 1):
+            for s in range(36):
+                ctx.load_sector(slot, s, b.cl[:100], b.row[:100])
+        ctx.find_links(0)
+        ctx.sync()
+        assert _launches(tpcca, stream, lambda: ctx.find_links(1))[-1][1] == (grid, 1, 1)
