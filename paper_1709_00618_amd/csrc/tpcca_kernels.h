@@ -15,6 +15,7 @@ struct RunHost {
   int32_t rows;  // how full the pad rows of the run's units are: a RowClass
   int32_t lds_unit;  // the run's units have at most this many hits (0: more), see unit_class
   int32_t many;      // the run has kManyUnits units or more (a captured launch's u1 is a capacity)
+  int32_t lists;     // the cleaning lists the chain starts (the chains do not go by units)
 };
 
 // By mean hits in a pad row: which kernels sort the rows and search the
@@ -44,6 +45,9 @@ constexpr int kManyUnits = 256;
 inline int unit_class(int64_t units, int64_t largest) {
   return units > kLdsUnits ? 0 : largest <= kLdsUnitSmall ? kLdsUnitSmall : largest <= kLdsUnit ? kLdsUnit : 0;
 }
+
+// The fit's order is by unit and start hit: what the chains by units give.
+inline bool plain_order(const ParamsDev &P) { return P.kf_split <= 0 && P.kf_bands <= 0 && P.kf_rows <= 0; }
 
 hipError_t launch_fill_i32(int32_t *p, int64_t n, int32_t v, hipStream_t s);
 hipError_t launch_fill_u64(unsigned long long *p, int64_t n, unsigned long long v, hipStream_t s);

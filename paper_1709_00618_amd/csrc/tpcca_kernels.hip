@@ -1859,7 +1859,7 @@ hipError_t launch_clean(const Bufs &B, const ParamsDev &P, int run, const RunHos
   const int nch = h.c1 - h.c0;
   if (nch > 0) {
     k_clean<<<grid_for(nch, 1, 8192), kBlock, 0, s>>>(B, run);
-    if (!h.lds_unit) list_starts(B, run, nch, s);
+    if (h.lists) list_starts(B, run, nch, s);
   }
   return hipGetLastError();
 }
@@ -1867,8 +1867,7 @@ hipError_t launch_clean(const Bufs &B, const ParamsDev &P, int run, const RunHos
 hipError_t launch_chains(const Bufs &B, const ParamsDev &P, int run, const RunHost &h,
                          hipStream_t s) {
   const int nch = h.c1 - h.c0, nu = h.u1 - h.u0;
-  const bool plain = P.kf_split <= 0 && P.kf_bands <= 0 && P.kf_rows <= 0;  // the order is by unit and start hit
-  if (h.lds_unit && plain && nu > 0) {
+  if (h.lds_unit && plain_order(P) && nu > 0) {
     const bool small = h.lds_unit == kLdsUnitSmall, many = h.many != 0;
     if (small || many) k_chain_units<kLdsUnitSmall, 512><<<grid_for(nu, 1, 2048), 512, 0, s>>>(B, P, run, P.n_rows, -1);
     if (!small)
@@ -1881,7 +1880,7 @@ hipError_t launch_chains(const Bufs &B, const ParamsDev &P, int run, const RunHo
     return hipGetLastError();
   }
   if (nch > 0) {
-    if (h.lds_unit) {  // the cleaning's lists are no longer there: clean again
+    if (!h.lists) {  // an order knob was set since, and the cleaning's lists are no longer there: clean again
       k_clean<<<grid_for(nch, 1, 8192), kBlock, 0, s>>>(B, run);
       list_starts(B, run, nch, s);
     }

@@ -127,7 +127,8 @@ static void drop_graphs(tpcca_ctx *c) {
 
 static bool same_capacities(const RunHost &a, const RunHost &b) {
   return a.u1 == b.u1 && a.c1 == b.c1 && a.cl1 == b.cl1 && a.bin1 == b.bin1 && a.trk_cap == b.trk_cap &&
-         a.tile1 == b.tile1 && a.rows == b.rows && a.lds_unit == b.lds_unit && a.many == b.many;
+         a.tile1 == b.tile1 && a.rows == b.rows && a.lds_unit == b.lds_unit && a.many == b.many &&
+         a.lists == b.lists;
 }
 
 static int dev_err(tpcca_ctx *c, hipError_t e, const char *what) {
@@ -368,6 +369,7 @@ static RunHost make_run(tpcca_ctx *c, int u0, int u1) {
   for (int u = u0; u < u1; ++u) largest = std::max(largest, c->units[u].n);
   h.lds_unit = unit_class(u1 - u0, largest);
   h.many = u1 - u0 >= kManyUnits ? 1 : 0;
+  h.lists = !h.lds_unit || !plain_order(c->P);
   return h;
 }
 
@@ -463,7 +465,8 @@ static int stage_call(tpcca_ctx *c, int slot, int sector, int stage) {
       if (c->uh[u].state != stage) return TPCCA_ESTATE;
   }
   for (int run : runs) {
-    const RunHost &h = c->runs[run];
+    RunHost &h = c->runs[run];
+    if (stage == kLinked) h.lists = !h.lds_unit || !plain_order(c->P);  // the knobs as they are now
     int rc = launch_stages(c, run, h, stage, stage);
     if (rc != TPCCA_OK) return rc;
     for (int u = h.u0; u < h.u1; ++u) c->uh[u].state = stage + 1;
@@ -1435,6 +1438,7 @@ extern "C" int tpcca_run_batch_noalloc(const tpcca_geometry_t *geo, const tpcca_
   h.rows = row_class(U, n_total, R);
   h.lds_unit = unit_class(U, largest);
   h.many = U >= kManyUnits ? 1 : 0;
+  h.lists = !h.lds_unit || !plain_order(P);
   RunDev &rd = H.runs[0];
   rd.u0 = h.u0;
   rd.u1 = h.u1;

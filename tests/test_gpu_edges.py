@@ -170,3 +170,18 @@ def test_link_blocks_per_cu_holds_for_sparse_rows(tpcca, torch_cuda, row_x, per_
         ctx.find_links(0)
         ctx.sync()
         assert _launches(tpcca, stream, lambda: ctx.find_links(1))[-1][1] == (grid, 1, 1)
+
+
+@pytest.mark.parametrize("knobs", [dict(fit_long_first=60), dict(fit_row_bands=4), dict(fit_rows=256)])
+def test_order_knobs_clean_once(tpcca, torch_cuda, row_x, knobs):
+    """With a knob that orders the fit otherwise, short units' chains go by the lists of
+    the cleaning: these are made there, and the chains do not clean again."""
+    stream = torch_cuda.cuda.Stream().cuda_stream
+    b = tpcgen.one_sector(seed=2)
+    with tpcca.Context(row_x, stream=stream) as ctx:
+        ctx.load_sector(0, 0, b.cl, b.row)
+        ctx.find_links()
+        ctx.sync()
+        ctx.set_tuning(**knobs)
+        clean = _launches(tpcca, stream, ctx.clean_links)[0][0]
+        assert clean not in [f for f, _ in _launches(tpcca, stream, ctx.build_tracklets)]
