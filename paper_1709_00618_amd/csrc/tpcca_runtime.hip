@@ -230,7 +230,7 @@ static void refresh_bufs(tpcca_ctx *c);
   X(upc, upc, int32_t, N, keepN)                                                 \
   X(dnc, dnc, int32_t, N, keepN)                                                 \
   X(flag, flag, int32_t, N, keepN)                                               \
-  X(starts, starts, int2, N, 0)                                                  \
+  X(starts, starts, int2, N, keepN)                                              \
   X(tiles, tiles, int4, NTILE, keepTiles)                                        \
   X(owner, owner, unsigned long long, N, keepN)                                  \
   X(trk_start, trk_start, int32_t, T, keepT)                                     \

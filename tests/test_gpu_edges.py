@@ -185,3 +185,27 @@ def test_order_knobs_clean_once(tpcca, torch_cuda, row_x, knobs):
         ctx.set_tuning(**knobs)
         clean = _launches(tpcca, stream, ctx.clean_links)[0][0]
         assert clean not in [f for f, _ in _launches(tpcca, stream, ctx.build_tracklets)]
+
+
+def test_buffers_that_grow_between_the_cleaning_and_the_chains(tpcca, row_x):
+    """A unit cleaned by lists (more than 40960 hits) keeps them when the next load
+    makes the work buffers grow before its chains are built."""
+    big = tpcgen.central_event(seed=8, n_tracks=12500, keep_truth=False)
+    units = [big.unit(u)[:2] for u in (4, 5, 6)]
+    assert units[0][0].shape[0] > 40960
+    with tpcca.Context(row_x) as ctx:
+        ctx.load_sector(0, 0, *units[0])
+        ctx.find_links()
+        ctx.clean_links()
+        for slot in (1, 2):
+            ctx.load_sector(slot, 0, *units[slot])
+        for slot in (1, 2):
+            ctx.find_links(slot)
+        ctx.build_tracklets(0)
+        for slot in (1, 2):
+            ctx.clean_links(slot)
+            ctx.build_tracklets(slot)
+        ctx.select_tracks()
+        ctx.sync()
+        for slot, (cl, row) in enumerate(units):
+            _parity.compare_unit_stagewise(ctx, slot, 0, cl, row, oracle.run_sector(cl, row, row_x))
