@@ -1483,7 +1483,7 @@ hipError_t p2_launch_decompress(const ParamsDev &P, const P2Params &q, const flo
   // 256, where the longest segment no longer sets the time, and at most four
   constexpr int kSimds = 1024;
   const int waves = n_seg <= 64 * kSimds ? (n_seg + 63) / 64 : kSimds * std::min(4, std::max(1, n_seg / (256 * kSimds)));
-  const int per = std::min(kDecSet, (n_seg + waves - 1) / waves);
+  const int per = (int)std::min<int64_t>(kDecSet, ((int64_t)n_seg + waves - 1) / waves);
   k_p2_decompress<<<waves, 64, 0, s>>>(P, q, row_x, n_seg, P.n_rows, per, n_hits, hit_begin, rec, res, yq, zq, rows);
   return hipGetLastError();
 }

@@ -209,3 +209,14 @@ def test_buffers_that_grow_between_the_cleaning_and_the_chains(tpcca, row_x):
         ctx.sync()
         for slot, (cl, row) in enumerate(units):
             _parity.compare_unit_stagewise(ctx, slot, 0, cl, row, oracle.run_sector(cl, row, row_x))
+
+
+@pytest.mark.parametrize("n_seg, waves, per", [(1, 1, 1), (65537, 1024, 65), (2 ** 31 - 4096, 4096, 1024),
+                                               (2 ** 31 - 1, 4096, 1024)])
+def test_decompression_split_up_to_the_largest_count(tpcca, torch_cuda, row_x, n_seg, waves, per):
+    """Waves and segments of a set, from the captured launch (nothing is run)."""
+    stream = torch_cuda.cuda.Stream().cuda_stream
+    with tpcca.Context(row_x, stream=stream) as ctx:
+        got = _launches(tpcca, stream, lambda: ctx.decompress(n_seg, *[4096] * 7),
+                        lambda k: (k.grid[0], ctypes.cast(k.args[5], ctypes.POINTER(ctypes.c_int32))[0]))
+    assert got == [(waves, per)]
