@@ -318,9 +318,9 @@ const char *tpcca_error_string(int status);
 const char *tpcca_last_error(tpcca_ctx_t *ctx);
 
 /* Stage timing of the last full stage sequence on ctx's stream, via HIP
-   events (ms): 0 grid, 1 links (the neighbour kernel alone), 2 clean,
-   3 chains (compaction), 4 Kalman fit (the fit kernel and the clearing of
-   the claim words it writes), 5 selection.  With timing on, a graph run of
+   events (ms): 0 grid, 1 links (the neighbour kernel alone), 2 clean (also
+   clears what the later stages write: start flags, claim words, assignment),
+   3 chains (compaction), 4 Kalman fit (the fit kernel alone), 5 selection.  With timing on, a graph run of
    tpcca_run_batch replays one graph per stage with the events between them
    on ctx's stream, so each replay times its own stages (the graphs are
    captured again when timing is switched).  Valid after tpcca_sync; returns

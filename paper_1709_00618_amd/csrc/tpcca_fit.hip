@@ -70,12 +70,19 @@ __device__ __forceinline__ void few_share(int n, int &lo, int &hi) {
 
 // A wave's share of many tracklets: a first share per wave, then shares
 // claimed from a work counter.  Up to kEqualShare per wave the first share is all
-// there is: with 104 to a wave (64 minimum-bias events) claims of 64 after the
-// first 64 went to two waves in three, and the fit took 2.76 ms; equal shares
-// take 2.50, of 85 (frame of 32 events) 2.33 instead of 2.87.  With more, claims
-// balance better: whole passes of two frames in flight and of one alone, claims
-// against equal shares, take 6.58 and 7.05 ms against 6.71 and 7.09 at 179 to a
-// wave (frames of 80 events), 7.92 and 8.55 against 8.45 and 8.81 at 215 (96).
+// there is: claims of 64 after the first 64 then go to some waves only.  Whole
+// passes on 4096 waves, claims against equal shares, of a batch or frame alone
+// and per batch of two in flight (us):
+//    67 to a wave (frame of 40 events)   2950 / 2970   2890 / 2850
+//   107 (64 minimum-bias events)         4885 / 4570   4625 / 4690
+//   113 (frame of 48 events)             4845 / 4495   4630 / 4625
+//   125 (80 minimum-bias events)         5605 / 5325   5470 / 5450
+//   135 (frame of 56 events)             5785 / 5340   5500 / 5550
+//   167 (64 events)                      6870 / 6345   6800 / 6795
+//   203 (80 events)                      8210 / 7685   8355 / 8360
+//   278 (128 events)                    10900 / 10275 11695 / 11660
+// Alone, evenness wins up to some 170; with two in flight the other batch fills
+// the uneven end, and claims win from some 100 on.  The line lies between.
 // Claims of at most half of what is left per wave, instead of four times that:
 // 128 events alone 10.90 -> 10.75 ms, two in flight 10.08 -> 10.19 per frame.
 constexpr int kEqualShare = 128;

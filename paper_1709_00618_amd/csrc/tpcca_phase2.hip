@@ -10,12 +10,14 @@
 //   compress  Sec. 3: track-model residuals of the quantised clusters, and
 //             the inverse
 //
-// One thread per segment (pairing, compression) or per final track (refit,
-// flags); the per-unit z-binned segment index keeps the pair search to the
-// facing ends within merge_dz_ends.  Every result is defined by comparisons
-// of (chi^2, key) or by sorted order, so the order threads run in never
-// matters.  Floating point as in the sector tracker: no contraction, fused
-// multiply-adds only where written, correctly rounded / and sqrt.
+// A lane per segment (outer end, compression), eight lanes per segment in the
+// enumeration of its candidate pairs, a lane per final track (refit), a thread
+// per cluster (flags); the per-unit z-binned segment index keeps the pair search
+// to the facing ends within merge_dz_ends.  Every result is defined by
+// comparisons of (chi^2, key) or by sorted order, so the order threads run in
+// never matters.  Floating point as in the sector tracker: no contraction, fused
+// multiply-adds only where written, correctly rounded quotients and roots (the
+// short forms of tpcca_kf.h in the ranges stated there, else the general ones).
 #include <hip/hip_runtime.h>
 #include <hipcub/hipcub.hpp>
 
@@ -1163,9 +1165,11 @@ __global__ __launch_bounds__(256) void k_p2_flags(Bufs B, P2Bufs Q, P2Params q, 
 // the residual, update).  Each wave has a set of `per` neighbouring segments,
 // takes them by length (a counting sort in LDS) and gives a lane the next one
 // when its own is done, so that lanes do not wait for the longest of 64
-// segments: a frame's have 1 to 159 hits, 51 on average.  Bound by instruction
+// segments: a frame's have up to 159 hits, 51 on average.  Bound by instruction
 // issue; 149 thousand segments 614 -> 226 us against a thread each in input
-// order.
+// order.  Segments shorter than tracks are (10 hits by default) cost more than a
+// thread each: 150 thousand of 3 hits 8 -> 13 us, of 6 hits 17 -> 24, of 10 hits
+// 43 -> 40.
 constexpr int kDecSet = 1024, kDecBins = 256;
 __global__ __launch_bounds__(64) void k_p2_decompress(ParamsDev P, P2Params q, const float *row_x, int n_seg, int R,
                                                      int per, const int32_t *n_hits, const int64_t *hit_begin,
@@ -1276,10 +1280,11 @@ __global__ void k_p2_fill_u8(uint8_t *p, int64_t n) {
     p[i] = 0;
 }
 // ---------------------------------------------------------------- order ---
-// Processing order of the persistent per-lane kernels (segment preparation
-// with compression, final refit): items by descending length, a counting
-// sort over kLenBins length classes.  A wave claims 64 consecutive items of
-// the order, so its lanes get about equally long work and finish together
+// Processing order of the per-lane kernels (segment preparation with
+// compression, final refit): items by descending length, a counting sort over
+// kLenBins length classes.  A wave takes 64 consecutive items of the order (the
+// preparation in strides; the refit its first by the wave's number and the next
+// ones by claims), so its lanes get about equally long work and finish together
 // instead of each wave waiting for the longest of 64 items in input order.
 // The order changes no result: each item's outputs depend on that item
 // alone.  Items of one length keep no particular order among themselves
