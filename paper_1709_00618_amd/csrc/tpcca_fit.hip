@@ -279,6 +279,11 @@ struct FitBlock {
   unsigned int steps, cands, tests, updates, iters;
 };
 
+// The set bits of a wave mask below this lane (no lane mask held in registers).
+__device__ __forceinline__ int lanes_below(unsigned long long m) {
+  return (int)__builtin_amdgcn_mbcnt_hi((unsigned int)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned int)m, 0u));
+}
+
 // Counts of the work done: of a lane or (all but cands in the totals) a wave.
 struct Work {
   unsigned int steps = 0, cands = 0, tests = 0, updates = 0, iters = 0;
@@ -466,7 +471,7 @@ template <int kBlk>
 __device__ __forceinline__ void fit_ended(const Bufs &B, FitBlock<kBlk> &S, bool fin, const Trk &k, int nh, float chi2,
                                           int Rs, int &n) {
   for (unsigned long long left = __ballot(fin); left;) {
-    const int lane = threadIdx.x & 63, at = n + __popcll(left & ((1ull << lane) - 1));
+    const int lane = threadIdx.x & 63, at = n + lanes_below(left);
     const bool put = (left >> lane & 1) && at < kDone;
     if (put)  // rows are as many as hits or more: a hit count has a row's size
       S.done[threadIdx.x >> 6][at] = make_int4(k.t, k.ucl, __float_as_int(chi2),
@@ -780,7 +785,7 @@ __device__ __forceinline__ void fit_many(const Bufs &B, const ParamsDev &P, RunD
       }
       if (ahead) {
         const int take = min(__popcll(idle), ahead);
-        const int rank = __popcll(idle & ((1ull << lane) - 1));
+        const int rank = lanes_below(idle);
         if (state == kFree && rank < take) {
           const int4 a = S.seed[wid][0][taken + rank], b = S.seed[wid][1][taken + rank],
                      c = S.seed[wid][2][taken + rank];
