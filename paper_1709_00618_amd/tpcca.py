@@ -369,7 +369,8 @@ class Context:
 
     # batches
     def run_batch(self, cl, row, units, device=False, graph=False):
-        """units: (U, 4) int array of (begin, n, slot, sector)."""
+        """units: (U, 4) int array of (begin, n, slot, sector).  Host input has
+        been copied on return; device input is read in place until sync()."""
         units = np.asarray(units, np.int64)
         self._bt = (np.ascontiguousarray(units[:, 2], np.int32), np.ascontiguousarray(units[:, 3], np.int32),
                     np.ascontiguousarray(units[:, 0], np.int64), np.ascontiguousarray(units[:, 1], np.int32))
